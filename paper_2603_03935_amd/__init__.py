@@ -442,7 +442,8 @@ def pack_masks(u8, stream=None):
     torch = _torch()
     m, h, w = u8.shape
     bits = torch.empty((m, h, (w + 63) // 64), dtype=torch.int64, device=u8.device)
-    src = u8.to(torch.uint8).contiguous()
+    # a bool's byte is taken as it is (the kernel tests for non-zero); other types are converted
+    src = (u8.view(torch.uint8) if u8.dtype == torch.bool else u8.to(torch.uint8)).contiguous()
     _check(load().disc_pack_masks(_ptr(src), m, h, w, _ptr(bits), _stream_handle(stream)))
     return bits
 

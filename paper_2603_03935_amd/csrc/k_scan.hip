@@ -1,6 +1,8 @@
 // Mask scan (bounding box + area per mask), which also appends each mask's
 // distance-transform work items to its class's lists (small batches; larger
 // ones build the lists in k_lists); the bit-packing and fill helpers.
+#include <algorithm>
+
 #include "disc_device.h"
 
 namespace disc {
@@ -380,27 +382,73 @@ void launch_copy_f32(const float* src, float* dst, int64_t n, hipStream_t st) {
   hipLaunchKernelGGL(k_copy_f32, dim3((unsigned)blocks), dim3(256), 0, st, src, dst, n);
 }
 
-// one thread per output word: 64 bytes -> 64 bits
-__global__ void k_pack(const uint8_t* u8, int m, int h, int w, uint64_t* bits) {
-  const int wq = (w + 63) / 64;
-  const int64_t nwords = (int64_t)m * h * wq;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nwords; i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t rowi = i / wq;
-    const int k = (int)(i - rowi * wq);
-    const uint8_t* src = u8 + rowi * w + 64 * k;
-    const int nb = min(64, w - 64 * k);
-    uint64_t v = 0;
-    for (int j = 0; j < nb; ++j) v |= (uint64_t)(src[j] != 0) << j;
-    bits[i] = v;
+// ---------------------------------------------------------------------------
+// Bit packing: 64 mask bytes -> one 64-bit word.  Bound by reading the bytes.
+// A thread turns 16 bytes (one load) into 16 bits and the four threads of a
+// word combine theirs across the quad, so a wavefront's load covers 1 KB in a
+// row; kPackUnroll independent loads per thread are in flight.  Rows start
+// anywhere (w need not be a multiple of 16, the caller's pointer may have any
+// alignment): the 16-byte loads are unaligned ones, which the hardware
+// splits; a chunk cut by the row's end is masked, and only the chunk that
+// would read past the buffer's last byte is read byte by byte.  One thread
+// per word reading its 64 bytes one at a time (64-byte strides across the
+// wavefront) took 168 us for 80 masks of 720x1280 (0.5 TB/s); a whole call
+// of this kernel takes 13 us (6.4 TB/s, part of it from the last-level cache).
+// ---------------------------------------------------------------------------
+constexpr int kPackUnroll = 4;
+
+// bit j of the result: byte j of d is not zero (the product gathers the four
+// flags, one per byte, into the low bits of the sum)
+__device__ __forceinline__ uint32_t nonzero_bytes8(uint32_t d0, uint32_t d1) {
+  const uint32_t f0 = ((((d0 & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | d0) >> 7) & 0x01010101u;
+  const uint32_t f1 = ((((d1 & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | d1) >> 7) & 0x01010101u;
+  return __builtin_amdgcn_udot4(f1, 0x80402010u, __builtin_amdgcn_udot4(f0, 0x08040201u, 0u, false), false);
+}
+
+__global__ __launch_bounds__(256) void k_pack(const uint8_t* u8, int64_t rows, int w, uint64_t* bits) {
+  const uint32_t cpr = 4u * (uint32_t)((w + 63) / 64);  // 16-byte chunks per row of words
+  const int64_t nchunk = rows * cpr, total = rows * w;
+  for (int64_t i0 = (int64_t)blockIdx.x * (256 * kPackUnroll); i0 < nchunk;
+       i0 += (int64_t)gridDim.x * (256 * kPackUnroll)) {
+    const int64_t row0 = i0 / cpr;
+    const uint32_t rem0 = (uint32_t)(i0 - row0 * cpr);
+    uint4 v[kPackUnroll];
+    int nb[kPackUnroll];  // bytes of the chunk inside its row
+#pragma unroll
+    for (int u = 0; u < kPackUnroll; ++u) {
+      const uint32_t j = rem0 + threadIdx.x + 256u * u, dr = j / cpr;
+      const int c = (int)(j - dr * cpr);
+      const int64_t row = row0 + dr, at = row * w + 16 * c;
+      nb[u] = row < rows ? min(16, w - 16 * c) : 0;
+      v[u] = make_uint4(0u, 0u, 0u, 0u);
+      if (nb[u] > 0) {
+        if (at + 16 <= total) {
+          __builtin_memcpy(&v[u], u8 + at, 16);
+        } else {
+          uint32_t q[4] = {0u, 0u, 0u, 0u};
+          for (int k = 0; k < nb[u]; ++k) q[k >> 2] |= (uint32_t)u8[at + k] << (8 * (k & 3));
+          v[u] = make_uint4(q[0], q[1], q[2], q[3]);
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kPackUnroll; ++u) {
+      uint32_t b = nonzero_bytes8(v[u].x, v[u].y) | (nonzero_bytes8(v[u].z, v[u].w) << 8);
+      if (nb[u] < 16) b &= nb[u] > 0 ? (1u << nb[u]) - 1u : 0u;
+      b <<= 16 * (threadIdx.x & 1);
+      b |= (uint32_t)__builtin_amdgcn_mov_dpp((int)b, 0xB1, 0xF, 0xF, true);  // the other half of the pair
+      const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)b, 0x4E, 0xF, 0xF, true);  // the other pair's half word
+      const int64_t i = i0 + threadIdx.x + 256 * u;
+      if ((threadIdx.x & 3) == 0 && i < nchunk) bits[i >> 2] = (uint64_t)b | ((uint64_t)hi << 32);
+    }
   }
 }
 
 void launch_pack(const uint8_t* u8, int m, int h, int w, uint64_t* bits, hipStream_t st) {
-  const int64_t nwords = (int64_t)m * h * ((w + 63) / 64);
-  if (nwords <= 0) return;
-  int64_t blocks = (nwords + 255) / 256;
-  if (blocks > 65536) blocks = 65536;
-  hipLaunchKernelGGL(k_pack, dim3((unsigned)blocks), dim3(256), 0, st, u8, m, h, w, bits);
+  const int64_t rows = (int64_t)m * h, nchunk = rows * 4 * ((w + 63) / 64);
+  if (nchunk <= 0) return;
+  const int64_t blocks = (nchunk + 256 * kPackUnroll - 1) / (256 * kPackUnroll);
+  hipLaunchKernelGGL(k_pack, dim3((unsigned)std::min<int64_t>(blocks, 1 << 20)), dim3(256), 0, st, u8, rows, w, bits);
 }
 
 }  // namespace disc
