@@ -1047,12 +1047,11 @@ disc_status disc_query_topk(const float* emb, int32_t m, const void* text, int32
     return fail(DISC_ERR_ALIGNMENT, "%s: pointers must be 16-byte aligned", who);
   Layout L{};
   L.staged_end = 0;
-  L.total = (size_t)round_up(4 * ((int64_t)m + q), 256);
+  L.total = (size_t)round_up((int64_t)query_ws_bytes(m, q, k), 256);
   Ctx cx;
   disc_status st;
   if ((st = acquire(static_cast<hipStream_t>(stream), L, nullptr, cx))) return st;
-  launch_query(emb, m, text, text_dtype == DISC_BF16, q, e, k, reinterpret_cast<float*>(cx.dev_ws), sim, scores, idx,
-               cx.st);
+  launch_query(emb, m, text, text_dtype == DISC_BF16, q, e, k, cx.dev_ws, sim, scores, idx, cx.st);
   if ((st = check_launch(who))) return st;
   return ok();
 }

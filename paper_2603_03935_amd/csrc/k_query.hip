@@ -6,8 +6,10 @@
 //   ties to the lower instance index.
 // The similarity matrix is one dense contraction (q x m, K = e) on FP32 MFMA
 // (v_mfma_f32_32x32x2f32, FP32 accumulation); the ranking is a per-query
-// selection that takes the k largest keys in k passes over the row.
+// selection over 64-bit keys held in registers.
+#include <algorithm>
 #include <type_traits>
+#include <utility>
 
 #include "disc_device.h"
 
@@ -84,40 +86,191 @@ __device__ __forceinline__ uint64_t rank_key(float s, int i) {
   return ((uint64_t)o << 32) | (uint32_t)(0xFFFFFFFFu - (uint32_t)i);
 }
 
-// one workgroup per query: k passes, each takes the largest key below the last
-__global__ __launch_bounds__(256) void k_topk(const float* sim, int m, int q, int k, float* scores, int32_t* idx) {
-  const int j = blockIdx.x;
-  if (j >= q) return;
-  const float* row = sim + (int64_t)j * m;
-  __shared__ uint64_t red[4];
-  uint64_t last = ~0ull;
-  for (int r = 0; r < k; ++r) {
-    uint64_t best = 0;
-    for (int i = threadIdx.x; i < m; i += 256) {
-      const uint64_t key = rank_key(row[i], i);
-      if (key < last && key > best) best = key;
+__device__ __forceinline__ float rank_score(uint64_t key) {
+  const uint32_t o = (uint32_t)(key >> 32);
+  return __uint_as_float((o & 0x80000000u) ? o ^ 0x80000000u : ~o);
+}
+
+__device__ __forceinline__ uint64_t max64(uint64_t a, uint64_t b) { return a > b ? a : b; }
+
+// The k largest keys of a row, larger first.  One workgroup takes up to
+// 1024 * VPT elements of a row, each thread VPT of them in registers (one
+// round of loads), and
+//  1. reduces them to group maxima (256 groups of four threads, or every
+//     thread's own for k > 64);
+//  2. one wavefront finds, bit by bit, a threshold T that at least k (and
+//     usually hardly more) group maxima reach: then at least k elements do, and
+//     any element below T has k larger ones;
+//  3. the elements that reach T (the expected count is close to k: for k = 10
+//     of 256 groups 10.2) are listed in LDS and each finds its rank by
+//     counting the larger ones.
+// Keys are distinct, so the result does not depend on the order of the list.
+// A row laid out so that one group holds most of the large elements can list
+// more than kTopkCand; it is then taken in k passes over the registers, each
+// the largest key below the last.  What bounds it is latency (three barriers
+// and the bit search), not the 4 bytes read per element: k dependent passes
+// over the row in memory took 111 us for 1024 rows of 8000 and 118 us for 5
+// rows of 20011 (k = 10), this kernel 12 and 7 us.
+//
+// KEYS = 0: the elements are a row of sim (element i's key from its score and
+// i); 1: keys of an earlier level, 0 where there is none.  FINAL: scores and
+// indices are written, (-inf, -1) past the last element; else the k keys (0
+// past the last) go to kout.
+constexpr int kTopkThreads = 1024;
+constexpr int kTopkCand = 2048;
+// elements per workgroup of the widest level-0 kernel: one level covers a row
+// of up to 32768 (20011 elements: 9 us; in four chunks and a second level, 15)
+constexpr int kTopkRow = 32 * kTopkThreads;
+constexpr int kTopkKeys = 8 * kTopkThreads;
+
+// T with at least k of the keys g (lane's NJ keys) at or above it, 0 if fewer
+// than k are non-zero; stops once at most about k / 4 more than k are
+template <int NJ>
+__device__ __forceinline__ uint64_t topk_threshold(const uint64_t* gk, int k) {
+  uint64_t g[NJ];
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) g[j] = gk[(threadIdx.x & 63) + 64 * j];
+  uint64_t T = 0;
+  for (int b = 63; b >= 0; --b) {
+    const uint64_t trial = T | (1ull << b);
+    int c = 0;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) c += __builtin_popcountll(__ballot(g[j] >= trial));
+    if (c >= k) {
+      T = trial;
+      if (c <= k + (k >> 2) + 2) break;
     }
-    for (int o = 32; o > 0; o >>= 1) {
-      const uint64_t t = __shfl_xor(best, o);
-      best = t > best ? t : best;
-    }
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = best;
-    __syncthreads();
-    best = red[0];
-    for (int w = 1; w < 4; ++w) best = red[w] > best ? red[w] : best;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      if (best == 0) {
-        idx[(int64_t)j * k + r] = -1;
-        scores[(int64_t)j * k + r] = -__builtin_inff();
-      } else {
-        const int i = (int)(0xFFFFFFFFu - (uint32_t)(best & 0xFFFFFFFFu));
-        idx[(int64_t)j * k + r] = i;
-        scores[(int64_t)j * k + r] = row[i];
-      }
-    }
-    last = best;
   }
+  return T;
+}
+
+template <int VPT, int KEYS, int FINAL>
+__global__ __launch_bounds__(kTopkThreads) void k_topk(const float* sim, const uint64_t* kin, int n, int k, int nch,
+                                                       uint64_t* kout, float* scores, int32_t* idx) {
+  const int64_t j = blockIdx.x / nch;
+  const int c0 = (int)(blockIdx.x % nch) * (kTopkThreads * VPT), tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  __shared__ uint64_t gk[kTopkThreads];
+  __shared__ uint64_t cand[kTopkCand];
+  __shared__ uint64_t Tsh;
+  __shared__ int nc_sh;
+  uint64_t key[VPT];
+  if (KEYS) {
+    const uint64_t* row = kin + j * n;
+#pragma unroll
+    for (int r = 0; r < VPT; ++r) {
+      const int i = c0 + r * kTopkThreads + tid;
+      key[r] = i < n ? row[i] : 0ull;
+    }
+  } else {
+    const float* row = sim + j * n;
+    float v[VPT];
+#pragma unroll
+    for (int r = 0; r < VPT; ++r) {
+      const int i = c0 + r * kTopkThreads + tid;
+      v[r] = i < n ? row[i] : 0.f;
+    }
+#pragma unroll
+    for (int r = 0; r < VPT; ++r) {
+      const int i = c0 + r * kTopkThreads + tid;
+      key[r] = i < n ? rank_key(v[r], i) : 0ull;
+    }
+  }
+  uint64_t best = 0;
+#pragma unroll
+  for (int r = 0; r < VPT; ++r) best = max64(best, key[r]);
+  const bool wide = k > 64;  // uniform
+  if (!wide) {
+    best = max64(best, __shfl_xor(best, 1));
+    best = max64(best, __shfl_xor(best, 2));
+    if ((tid & 3) == 0) gk[tid >> 2] = best;
+  } else {
+    gk[tid] = best;
+  }
+  if (tid == 0) nc_sh = 0;
+  __syncthreads();
+  if (wv == 0) {
+    const uint64_t T = wide ? topk_threshold<kTopkThreads / 64>(gk, k) : topk_threshold<4>(gk, k);
+    if (lane == 0) Tsh = T;
+  }
+  __syncthreads();
+  const uint64_t T = max64(Tsh, 1ull);  // key 0 is no element
+#pragma unroll
+  for (int r = 0; r < VPT; ++r)
+    if (key[r] >= T) {
+      const int p = atomicAdd(&nc_sh, 1);
+      if (p < kTopkCand) cand[p] = key[r];
+    }
+  __syncthreads();
+  const int nc = nc_sh;
+  const int64_t o = FINAL ? j * k : (int64_t)blockIdx.x * k;
+  auto emit = [&](int rank, uint64_t q) {
+    if (FINAL) {
+      scores[o + rank] = q ? rank_score(q) : -__builtin_inff();
+      idx[o + rank] = q ? (int)(0xFFFFFFFFu - (uint32_t)q) : -1;
+    } else {
+      kout[o + rank] = q;
+    }
+  };
+  if (nc <= kTopkCand) {
+    for (int c = tid; c < nc; c += kTopkThreads) {
+      const uint64_t q = cand[c];
+      int rank = 0;
+#pragma unroll 4
+      for (int i = 0; i < nc; ++i) rank += cand[i] > q ? 1 : 0;
+      if (rank < k) emit(rank, q);
+    }
+    for (int r = nc + tid; r < k; r += kTopkThreads) emit(r, 0ull);
+  } else {
+    uint64_t last = ~0ull;
+    for (int r = 0; r < k; ++r) {
+      uint64_t top = 0;
+#pragma unroll
+      for (int i = 0; i < VPT; ++i)
+        if (key[i] < last && key[i] > top) top = key[i];
+      for (int s = 32; s > 0; s >>= 1) top = max64(top, __shfl_xor(top, s));
+      if (lane == 0) gk[wv] = top;
+      __syncthreads();
+      for (int w = 0; w < kTopkThreads / 64; ++w) top = max64(top, gk[w]);
+      __syncthreads();
+      if (tid == 0) emit(r, top);
+      last = top;
+    }
+  }
+}
+
+static int topk_chunks(int64_t n, int per) { return (int)std::max<int64_t>(1, (n + per - 1) / per); }
+
+// Scratch keys of the levels below the last (none for a row of one chunk):
+// two buffers, each a level's output.
+static void topk_scratch(int m, int q, int k, int64_t* a, int64_t* b) {
+  *a = *b = 0;
+  const int nch = topk_chunks(m, kTopkRow);
+  if (nch == 1) return;
+  *a = (int64_t)q * nch * k;
+  const int nch2 = topk_chunks((int64_t)nch * k, kTopkKeys);
+  if (nch2 > 1) *b = (int64_t)q * nch2 * k;
+}
+
+static void launch_topk(const float* sim, int m, int q, int k, uint64_t* ka, uint64_t* kb, float* scores, int32_t* idx,
+                        hipStream_t st) {
+  const int nch = topk_chunks(m, kTopkRow);
+  const dim3 blk(kTopkThreads);
+  if (nch == 1) {
+    // a row of at most 8192 leaves three quarters of the wide kernel's registers empty
+    if (m <= 8 * kTopkThreads) hipLaunchKernelGGL((k_topk<8, 0, 1>), dim3(q), blk, 0, st, sim, nullptr, m, k, 1, nullptr, scores, idx);
+    else hipLaunchKernelGGL((k_topk<32, 0, 1>), dim3(q), blk, 0, st, sim, nullptr, m, k, 1, nullptr, scores, idx);
+    return;
+  }
+  hipLaunchKernelGGL((k_topk<32, 0, 0>), dim3((unsigned)(q * nch)), blk, 0, st, sim, nullptr, m, k, nch, ka, nullptr, nullptr);
+  int n = nch * k;  // keys per row of the level before
+  for (;;) {
+    const int c = topk_chunks(n, kTopkKeys);
+    if (c == 1) break;
+    hipLaunchKernelGGL((k_topk<8, 1, 0>), dim3((unsigned)(q * c)), blk, 0, st, nullptr, ka, n, k, c, kb, nullptr, nullptr);
+    std::swap(ka, kb);
+    n = c * k;
+  }
+  hipLaunchKernelGGL((k_topk<8, 1, 1>), dim3(q), blk, 0, st, nullptr, ka, n, k, 1, nullptr, scores, idx);
 }
 
 // ---------------------------------------------------------------------------
@@ -215,10 +368,20 @@ void launch_heatmap(const void* tok, int tok_dtype, const float* scale, int G, i
     hipLaunchKernelGGL(k_sim<0>, grid, dim3(256), 0, st, Y, G, text, q, E, fac, inv_text, heat);
 }
 
-void launch_query(const float* emb, int m, const void* text, int text_bf16, int q, int e, int k, float* inv,
+size_t query_ws_bytes(int m, int q, int k) {
+  int64_t a, b;
+  topk_scratch(m, q, k, &a, &b);
+  return 8 * (size_t)(a + b) + 4 * ((size_t)m + q);
+}
+
+void launch_query(const float* emb, int m, const void* text, int text_bf16, int q, int e, int k, char* ws,
                   float* sim, float* scores, int32_t* idx, hipStream_t st) {
-  float* inv_emb = inv;
-  float* inv_text = inv + m;
+  int64_t na, nb;
+  topk_scratch(m, q, k, &na, &nb);
+  uint64_t* ka = reinterpret_cast<uint64_t*>(ws);
+  uint64_t* kb = ka + na;
+  float* inv_emb = reinterpret_cast<float*>(kb + nb);
+  float* inv_text = inv_emb + m;
   if (m > 0) hipLaunchKernelGGL(k_invnorm<0>, dim3((m + 3) / 4), dim3(256), 0, st, emb, m, e, inv_emb);
   if (text_bf16)
     hipLaunchKernelGGL(k_invnorm<1>, dim3((q + 3) / 4), dim3(256), 0, st, text, q, e, inv_text);
@@ -231,7 +394,7 @@ void launch_query(const float* emb, int m, const void* text, int text_bf16, int 
     else
       hipLaunchKernelGGL(k_sim<0>, grid, dim3(256), 0, st, emb, m, text, q, e, inv_emb, inv_text, sim);
   }
-  hipLaunchKernelGGL(k_topk, dim3(q), dim3(256), 0, st, sim, m, q, k, scores, idx);
+  launch_topk(sim, m, q, k, ka, kb, scores, idx, st);
 }
 
 }  // namespace disc
