@@ -5,7 +5,7 @@
 //   for each query j, the k instances of highest similarity, higher first,
 //   ties to the lower instance index.
 // The similarity matrix is one dense contraction (q x m, K = e) on FP32 MFMA
-// (v_mfma_f32_32x32x2f32, FP32 accumulation); the ranking is a per-query
+// (FP32 accumulation); the ranking is a per-query
 // selection over 64-bit keys held in registers.
 #include <algorithm>
 #include <type_traits>
@@ -16,6 +16,7 @@
 namespace disc {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 template <int BF16>
 __device__ __forceinline__ float4 load_row4(const void* base, int64_t off) {
@@ -29,54 +30,208 @@ __device__ __forceinline__ float4 load_row4(const void* base, int64_t off) {
 
 // inv[r] = 1 / ||row r|| (0 for a zero row); one wavefront per row
 template <int BF16>
-__global__ __launch_bounds__(256) void k_invnorm(const void* x, int rows, int e, float* inv) {
-  const int r = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (r >= rows) return;
+__device__ __forceinline__ void invnorm_row(const void* x, int64_t r, int e, float* inv) {
+  const int lane = threadIdx.x & 63;
   float a = 0.f;
   for (int c = lane * 4; c < e; c += 256) {
-    const float4 v = load_row4<BF16>(x, (int64_t)r * e + c);
+    const float4 v = load_row4<BF16>(x, r * e + c);
     a += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
   }
   for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o);
   if (lane == 0) inv[r] = a > 0.f ? 1.0f / __builtin_sqrtf(a) : 0.f;
 }
 
-// sim tile: 64 queries x 64 instances per workgroup (4 wavefronts of 32 x 32),
-// K in steps of 16 staged through LDS.
+// rows 0 .. m - 1 of the result: emb; rows m .. m + q - 1: text
 template <int BF16>
-__global__ __launch_bounds__(256) void k_sim(const float* emb, int m, const void* text, int q, int e,
-                                             const float* inv_emb, const float* inv_text, float* sim) {
-  constexpr int BK = 16;
-  const int q0 = blockIdx.y * 64, i0 = blockIdx.x * 64;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, wq = wv >> 1, wi = wv & 1;
-  __shared__ float Ts[64][BK + 1];
-  __shared__ float Ys[64][BK + 1];
-  floatx16 acc = {};
-  // loaders: 64 rows x 16 k = 1024 floats per operand, 4 per thread
-  const int lr = tid >> 2, lk = (tid & 3) * 4;
-  for (int k0 = 0; k0 < e; k0 += BK) {
-    const float4 tv = q0 + lr < q ? load_row4<BF16>(text, (int64_t)(q0 + lr) * e + k0 + lk) : make_float4(0.f, 0.f, 0.f, 0.f);
-    const float4 yv = i0 + lr < m ? *reinterpret_cast<const float4*>(emb + (int64_t)(i0 + lr) * e + k0 + lk)
-                                  : make_float4(0.f, 0.f, 0.f, 0.f);
-    __syncthreads();
-    Ts[lr][lk] = tv.x; Ts[lr][lk + 1] = tv.y; Ts[lr][lk + 2] = tv.z; Ts[lr][lk + 3] = tv.w;
-    Ys[lr][lk] = yv.x; Ys[lr][lk + 1] = yv.y; Ys[lr][lk + 2] = yv.z; Ys[lr][lk + 3] = yv.w;
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < BK; kk += 2) {
-      const float a = Ts[32 * wq + (lane & 31)][kk + (lane >> 5)];
-      const float bb = Ys[32 * wi + (lane & 31)][kk + (lane >> 5)];
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a, bb, acc, 0, 0, 0);
+__global__ __launch_bounds__(256) void k_invnorms(const float* emb, int m, const void* text, int q, int e,
+                                                  float* inv_emb, float* inv_text) {
+  const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (r < m) invnorm_row<0>(emb, r, e, inv_emb);
+  else if (r - m < q) invnorm_row<BF16>(text, r - m, e, inv_text);
+}
+
+// FP32 contraction of rows of A with rows of B (both with the K elements of a
+// row contiguous): a workgroup of WA x WB = 4 wavefronts computes MT WA rows
+// of A by MT WB rows of B, a wavefront one MT x MT tile, MT = 32
+// (v_mfma_f32_32x32x2f32) or 16 (v_mfma_f32_16x16x4f32).  FP32 MFMA adds its
+// products one k after the other, each addition rounded like an fma's (checked
+// bit for bit against an fma chain), so every shape gives the same bits.
+//
+// Bound by the FP32 matrix rate for many rows of A and by reading B for few.
+// K is staged through LDS, BK at a time in two buffers.  In a step, the
+// operands of each group of four MFMAs are read while the group before runs;
+// before the last but one group the next step's elements, fetched a whole
+// step earlier, are stored to the other buffer and the fetch of the step after
+// is issued; the step's one barrier stands before the last group, whose
+// operands are in registers by then.  So no wavefront waits for a load, an
+// LDS read or a store with its matrix core idle.  A row's elements are stored
+// in the order in which the lanes take them (all elements of one lane group
+// of four consecutive MFMAs together), so an operand of four MFMAs is one
+// 16-byte LDS read; the row stride BK + 4 keeps those reads free of bank
+// conflicts.
+template <int MT, int WA, int WB, int BK>
+struct GemmTile {
+  static constexpr int KG = MT == 32 ? 2 : 4;  // K of one MFMA
+  static constexpr int TA = MT * WA, TB = MT * WB, LD = BK + 4;
+  static constexpr int QA = TA * BK / 1024, QB = TB * BK / 1024;  // 16-byte loads per thread and step
+  static constexpr int NG = BK / (4 * KG);                        // operand groups of a step
+  static_assert(WA * WB == 4 && QA * 1024 == TA * BK && QB * 1024 == TB * BK && NG % 2 == 0, "tile");
+  typedef typename std::conditional<MT == 32, floatx16, floatx4>::type Acc;
+  static constexpr int NV = MT * MT / 64;
+  alignas(16) float as[2][TA][LD];
+  alignas(16) float bs[2][TB][LD];
+
+  // rows of A and B (within the workgroup's tile) of accumulator element v of this lane
+  static __device__ __forceinline__ int row_a(int v) {
+    const int lane = threadIdx.x & 63, wa = (threadIdx.x >> 6) / WB;
+    return MT * wa + (MT == 32 ? 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3) : 4 * (lane >> 4) + v);
+  }
+  static __device__ __forceinline__ int row_b() { return MT * ((threadIdx.x >> 6) % WB) + (threadIdx.x & (MT - 1)); }
+
+  // place of elements k .. k + 3 (k % 4 == 0) in their row
+  static __device__ __forceinline__ int slot(int k) {
+    return MT == 32 ? (k & ~7) + ((k >> 1) & 3) : (k & ~15) + ((k >> 2) & 3);
+  }
+  static __device__ __forceinline__ void put(float* p, floatx4 v) {
+    if (MT == 32) {
+      *reinterpret_cast<float2*>(p) = make_float2(v.x, v.z);
+      *reinterpret_cast<float2*>(p + 4) = make_float2(v.y, v.w);
+    } else {
+      p[0] = v.x; p[4] = v.y; p[8] = v.z; p[12] = v.w;
     }
   }
-  const int i = i0 + 32 * wi + (lane & 31);
-  if (i >= m) return;
-  const float yi = inv_emb[i];
+
+  // sum over k < e of A[row_a] B[row_b]; load_a(row, k) and load_b(row, k)
+  // give elements k .. k + 3 of a row of the tile (k % 4 == 0, below e)
+  template <class LA, class LB>
+  __device__ __forceinline__ Acc run(int e, LA load_a, LB load_b) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    // whole vectors, so that the loads write them in place; 256 threads cover
+    // 1024 / BK rows a round, so a thread's k is the same in each
+    floatx4 ra[QA], rb[QB];
+    constexpr int RR = 1024 / BK;
+    const int kt = 4 * (tid % (BK / 4)), rt = tid / (BK / 4);
+    auto fetch = [&](int k0) {  // past the end: the last elements again
+      const int k = min(k0 + kt, e - 4);
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const int j = q0 + 32 * wq + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-    if (j < q) sim[(int64_t)j * m + i] = acc[v] * yi * inv_text[j];
+      for (int i = 0; i < QA; ++i) {
+        const float4 v = load_a(rt + i * RR, k);
+        ra[i] = floatx4{v.x, v.y, v.z, v.w};
+      }
+#pragma unroll
+      for (int i = 0; i < QB; ++i) {
+        const float4 v = load_b(rt + i * RR, k);
+        rb[i] = floatx4{v.x, v.y, v.z, v.w};
+      }
+    };
+    // The loaded vectors pass through an empty asm where they are stored:
+    // without it the register moves that pair up a store's elements are placed
+    // right after the loads, and wait for them there.
+    auto here = [](floatx4& v) { asm volatile("" : "+v"(v)); };
+    auto store = [&](int buf, int k0) {
+#pragma unroll
+      for (int i = 0; i < QA; ++i) here(ra[i]);
+#pragma unroll
+      for (int i = 0; i < QB; ++i) here(rb[i]);
+      if (k0 + BK > e) {  // K past e: zeros, which leave every sum's bits as they are
+        const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < QA; ++i) ra[i] = k0 + kt < e ? ra[i] : zero;
+#pragma unroll
+        for (int i = 0; i < QB; ++i) rb[i] = k0 + kt < e ? rb[i] : zero;
+      }
+      float* pa = as[buf][rt] + slot(kt);
+      float* pb = bs[buf][rt] + slot(kt);
+#pragma unroll
+      for (int i = 0; i < QA; ++i) put(pa + i * RR * LD, ra[i]);
+#pragma unroll
+      for (int i = 0; i < QB; ++i) put(pb + i * RR * LD, rb[i]);
+    };
+    fetch(0);
+    store(0, 0);
+    fetch(BK);
+    __syncthreads();
+    const int arow = MT * ((tid >> 6) / WB) + (lane & (MT - 1)), brow = row_b(), lg = 4 * (lane / MT);
+    float4 a[2], b[2];
+    auto read = [&](int buf, int g, int set) {
+      a[set] = *reinterpret_cast<const float4*>(&as[buf][arow][4 * KG * g + lg]);
+      b[set] = *reinterpret_cast<const float4*>(&bs[buf][brow][4 * KG * g + lg]);
+    };
+    Acc acc = {};
+    read(0, 0, 0);
+    int buf = 0;
+    for (int k0 = 0; k0 < e; k0 += BK, buf ^= 1) {
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        if (g + 1 < NG) {
+          read(buf, g + 1, (g + 1) & 1);
+          if (g + 2 == NG) {  // (past the last step nothing reads what is stored)
+            store(buf ^ 1, k0 + BK);
+            fetch(k0 + 2 * BK);
+          }
+        } else {
+          __syncthreads();
+          read(buf ^ 1, 0, (g + 1) & 1);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const float x = (&a[g & 1].x)[s], y = (&b[g & 1].x)[s];
+          if constexpr (MT == 32) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x, y, acc, 0, 0, 0);
+          else acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x, y, acc, 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    return acc;
   }
+};
+
+// sim[j][i] = (text_j . emb_i) inv_emb[i] inv_text[j].  The workgroups of one
+// XCD take consecutive tiles, query tiles first, so that a tile of instances
+// is read from HBM by one XCD.
+template <int BF16, int MT, int WA, int WB, int BK>
+__global__ __launch_bounds__(256) void k_sim(const float* emb, int m, const void* text, int q, int e,
+                                             const float* inv_emb, const float* inv_text, float* sim, int qt) {
+  typedef GemmTile<MT, WA, WB, BK> Tile;
+  __shared__ Tile tile;
+  const int b = xcd_remap(blockIdx.x, gridDim.x);
+  const int q0 = b % qt * Tile::TA, i0 = b / qt * Tile::TB;
+  const typename Tile::Acc acc =
+      tile.run(e, [&](int r, int k) { return load_row4<BF16>(text, (int64_t)min(q0 + r, q - 1) * e + k); },
+               [&](int r, int k) { return load_row4<0>(emb, (int64_t)min(i0 + r, m - 1) * e + k); });
+  const int i = i0 + Tile::row_b();
+  const float yi = inv_emb[min(i, m - 1)];
+  float tj[Tile::NV];  // all loads before the first store
+#pragma unroll
+  for (int v = 0; v < Tile::NV; ++v) tj[v] = inv_text[min(q0 + Tile::row_a(v), q - 1)];
+#pragma unroll
+  for (int v = 0; v < Tile::NV; ++v) {
+    const int j = q0 + Tile::row_a(v);
+    if (j < q && i < m) sim[(int64_t)j * m + i] = acc[v] * yi * tj[v];
+  }
+}
+
+// Tile by size (us of the whole query call at width 768 or 1024, 16 x 64 / 32
+// x 32 / 64 x 64; the 64 x 64 kernel before, K step 16 and two barriers a
+// step, took 182 us for 1024 x 8000 alone, now 145):
+//   q x m          5 x 20011   16 x 5000   64 x 3000   512 x 3000   1024 x 3000   1024 x 8000
+//                  31/34/49    20/19/32    17/17/25    49/45/49     94/87/76      210/189/165
+// Few queries are bound by reading the instances: the fewer of a tile's query
+// rows are padding, the better.  The larger tile reads less through LDS per
+// product but has a quarter of the workgroups and four times the chain of
+// dependent MFMAs: it wins from about two tiles per CU on.
+template <int BF16>
+static void launch_sim(const float* emb, int m, const void* text, int q, int e, const float* inv_emb,
+                       const float* inv_text, float* sim, hipStream_t st) {
+  auto tiles = [&](int ta, int tb) { return (int64_t)((q + ta - 1) / ta) * ((m + tb - 1) / tb); };
+  auto go = [&](auto kernel, int ta, int tb) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)tiles(ta, tb)), dim3(256), 0, st, emb, m, text, q, e, inv_emb, inv_text, sim,
+                       (q + ta - 1) / ta);
+  };
+  if (q <= 16) go(k_sim<BF16, 16, 1, 4, 64>, 16, 64);
+  else if (tiles(64, 64) < 512) go(k_sim<BF16, 16, 2, 2, 64>, 32, 32);
+  else go(k_sim<BF16, 32, 2, 2, 32>, 64, 64);
 }
 
 // Order-preserving 64-bit key: larger score first, then smaller index.
@@ -357,15 +512,13 @@ void launch_heatmap(const void* tok, int tok_dtype, const float* scale, int G, i
   else if (tok_dtype == 1) { if (p_bf16) proj(O{}, O{}); else proj(O{}, Z{}); }
   else { if (p_bf16) proj(T2{}, O{}); else proj(T2{}, Z{}); }
   hipLaunchKernelGGL(k_heat_factor, dim3((G + 3) / 4), dim3(256), 0, st, Y, G, E, D, fac);
-  if (text_bf16)
-    hipLaunchKernelGGL(k_invnorm<1>, dim3((q + 3) / 4), dim3(256), 0, st, text, q, E, inv_text);
-  else
-    hipLaunchKernelGGL(k_invnorm<0>, dim3((q + 3) / 4), dim3(256), 0, st, text, q, E, inv_text);
-  const dim3 grid((G + 63) / 64, (q + 63) / 64);
-  if (text_bf16)
-    hipLaunchKernelGGL(k_sim<1>, grid, dim3(256), 0, st, Y, G, text, q, E, fac, inv_text, heat);
-  else
-    hipLaunchKernelGGL(k_sim<0>, grid, dim3(256), 0, st, Y, G, text, q, E, fac, inv_text, heat);
+  if (text_bf16) {
+    hipLaunchKernelGGL(k_invnorms<1>, dim3((q + 3) / 4), dim3(256), 0, st, nullptr, 0, text, q, E, nullptr, inv_text);
+    launch_sim<1>(Y, G, text, q, E, fac, inv_text, heat, st);
+  } else {
+    hipLaunchKernelGGL(k_invnorms<0>, dim3((q + 3) / 4), dim3(256), 0, st, nullptr, 0, text, q, E, nullptr, inv_text);
+    launch_sim<0>(Y, G, text, q, E, fac, inv_text, heat, st);
+  }
 }
 
 size_t query_ws_bytes(int m, int q, int k) {
@@ -382,17 +535,12 @@ void launch_query(const float* emb, int m, const void* text, int text_bf16, int 
   uint64_t* kb = ka + na;
   float* inv_emb = reinterpret_cast<float*>(kb + nb);
   float* inv_text = inv_emb + m;
-  if (m > 0) hipLaunchKernelGGL(k_invnorm<0>, dim3((m + 3) / 4), dim3(256), 0, st, emb, m, e, inv_emb);
-  if (text_bf16)
-    hipLaunchKernelGGL(k_invnorm<1>, dim3((q + 3) / 4), dim3(256), 0, st, text, q, e, inv_text);
-  else
-    hipLaunchKernelGGL(k_invnorm<0>, dim3((q + 3) / 4), dim3(256), 0, st, text, q, e, inv_text);
+  const dim3 ng((unsigned)(((int64_t)m + q + 3) / 4));
+  if (text_bf16) hipLaunchKernelGGL(k_invnorms<1>, ng, dim3(256), 0, st, emb, m, text, q, e, inv_emb, inv_text);
+  else hipLaunchKernelGGL(k_invnorms<0>, ng, dim3(256), 0, st, emb, m, text, q, e, inv_emb, inv_text);
   if (m > 0) {
-    const dim3 grid((m + 63) / 64, (q + 63) / 64);
-    if (text_bf16)
-      hipLaunchKernelGGL(k_sim<1>, grid, dim3(256), 0, st, emb, m, text, q, e, inv_emb, inv_text, sim);
-    else
-      hipLaunchKernelGGL(k_sim<0>, grid, dim3(256), 0, st, emb, m, text, q, e, inv_emb, inv_text, sim);
+    if (text_bf16) launch_sim<1>(emb, m, text, q, e, inv_emb, inv_text, sim, st);
+    else launch_sim<0>(emb, m, text, q, e, inv_emb, inv_text, sim, st);
   }
   launch_topk(sim, m, q, k, ka, kb, scores, idx, st);
 }
