@@ -35,6 +35,7 @@
 //     and sums sqrt(e) over each patch (segmented lane reduction per patch
 //     row; a patch row split between two bands is finished in fixed order).
 #include <mutex>
+#include <type_traits>
 
 #include "disc_device.h"
 
@@ -678,25 +679,59 @@ __host__ __device__ constexpr int direct_items(int c) { return c == 5 ? 1 : (kEd
 // run lengths past a strip window's ends are needed up to the largest g the
 // tables keep (576, the bound of the tallest class); AREA needs only g > 0
 constexpr int kDirRunCap = 576;
-constexpr int kDirRows = 4;   // rows searched together
-constexpr int kDirSteps = 4;  // distances per search step (windows start on 4-row words)
-// A group's search reads at most kDirRows + kDirSteps - 2 rows past its item
-// on either side (a row that is done keeps being updated while another row of
-// its group searches; a step visits kDirSteps distances): zeroed guard rows
-// at the ends of the table, real rows of the neighbouring slot elsewhere
-// (every slot row is written, 0 past its item, so every value read is a
-// g <= 8448 and the arithmetic cannot overflow; a candidate read past the
-// item can no longer win).
-constexpr int kDirGuard = 12;
-static_assert(kDirGuard >= kDirRows + kDirSteps - 2 && kDirGuard % 4 == 0, "guard rows");
-static_assert(kDirRows == 4 && kDirSteps == 4 && kBlkRows % kDirRows == 0, "search windows are whole 4-row words");
+constexpr int kDirRows = 8;   // rows searched together
+constexpr int kDirSteps = 8;  // distances per search step
+// A group's search reads past its item (a row that is done keeps being updated
+// while another row of its group searches; a step visits kDirSteps distances,
+// and windows are whole 8-row blocks): a step starts while d is below some
+// row's distance to the padding row on that side, so it reads down to
+// row -kDirTop and up to row n + 13.  Guard rows at the ends of the table,
+// rows of the neighbouring slot elsewhere (every slot row is written); a
+// candidate read past the item can no longer win.  Guard entries are 0, the
+// farthest a candidate can be.
+constexpr int kDirTop = 8, kDirBottom = 16;
+static_assert(kDirRows == 8 && kDirSteps == 8 && kBlkRows % kDirRows == 0, "search windows are whole 8-row blocks");
+
+// Ends of the work sub-lists of every class (running sums), read once per
+// workgroup: an item's place in the lists is then found without a chain of
+// loads.  All threads of the block call direct_lists.
+struct DirLists {
+  int end[kClasses][kLists];
+};
+__device__ __forceinline__ void direct_lists(const int32_t* counts, int item_cap, DirLists& li) {
+  static_assert(kClasses * kLists <= 64, "one wavefront reads the counts");
+  if (threadIdx.x < 64) {
+    const int lane = threadIdx.x;
+    int x = lane < kClasses * kLists ? min(counts[lane], item_cap) : 0;
+    for (int o = 1; o < kLists; o <<= 1) {
+      const int t = __shfl_up(x, o, kLists);
+      if ((lane & (kLists - 1)) >= o) x += t;
+    }
+    if (lane < kClasses * kLists) li.end[lane / kLists][lane % kLists] = x;
+  }
+  __syncthreads();
+}
+// item word k of class c (k below the class's count)
+__device__ __forceinline__ const int32_t* direct_item_at(const DirLists& li, const int32_t* items, int item_cap, int c,
+                                                         int k) {
+  int j = 0, before = 0;
+#pragma unroll
+  for (int q = 0; q < kLists - 1; ++q) {
+    const int e = li.end[c][q];
+    if (k >= e) {
+      j = q + 1;
+      before = e;
+    }
+  }
+  return items + ((int64_t)c * kLists + j) * item_cap + (k - before);
+}
 
 // the packets of the classes in the kernel's range (tallest first)
-__device__ __forceinline__ int direct_count(const int32_t* counts, int item_cap, bool tall, int* cnt) {
+__device__ __forceinline__ int direct_count(const DirLists& li, bool tall, int* cnt) {
   int total = 0;
 #pragma unroll
   for (int c = 0; c < kClasses; ++c) {
-    cnt[c] = tall == (c == 5) ? class_count(counts, item_cap, c) : 0;
+    cnt[c] = tall == (c == 5) ? __builtin_amdgcn_readfirstlane(li.end[c][kLists - 1]) : 0;
     total += (cnt[c] + direct_items(c) - 1) / direct_items(c);
   }
   return total;
@@ -720,16 +755,93 @@ __device__ __forceinline__ int direct_packet_class(const int* cnt, int p, int& f
   }
   return -1;
 }
+// A row's strip window (bits [xs, xs + 64)) and the unbroken runs of mask
+// pixels past its two ends, where the window's own end bits are set: their
+// lengths, or at least kDirRunCap (the tables clamp g at 576 or below).  No bit
+// outside columns x0 .. x1 is set, so words outside are not read (this also
+// keeps out the bits past the frame's width).  The window and one word to
+// each side are loaded together, then four more words a side at a time while
+// a run goes on: one word at a time, a row of a wide mask was a chain of up to
+// ten dependent loads (whole kernel at 8 masks of 336x336: 25.1 -> 23.1 us).
+__device__ __forceinline__ void row_window(const uint64_t* row, int xs, int x0, int x1, uint64_t& win, int& L, int& R) {
+  const int k = xs >> 6, b = xs & 63, ka = x0 >> 6, kz = x1 >> 6;
+  const uint64_t first = ~0ull << (x0 & 63), last = ~0ull >> (63 - (x1 & 63));
+  auto word = [&](int q) {
+    const bool in = q >= ka && q <= kz;
+    uint64_t w = row[min(max(q, ka), kz)];
+    if (q == ka) w &= first;
+    if (q == kz) w &= last;
+    return in ? w : 0ull;
+  };
+  const uint64_t wl = word(k - 1), w0 = word(k), w1 = word(k + 1), w2 = word(k + 2);
+  win = b ? (w0 >> b) | (w1 << (64 - b)) : w0;
+  L = R = 0;
+  auto ones_down = [](uint64_t w) { return ~w ? __builtin_clzll(~w) : 64; };  // set bits from bit 63 down
+  auto ones_up = [](uint64_t w) { return ~w ? __builtin_ctzll(~w) : 64; };
+  int left = 0, right = 0;  // where a run that is still going on reads next
+  bool gl = false, gr = false;
+  if (win & 1ull) {
+    L = b ? min(ones_down(w0 << (64 - b)), b) : 0;
+    if (L == b) {
+      const int o = ones_down(wl);
+      L += o;
+      gl = o == 64;
+      left = k - 2;
+    }
+  }
+  if (win >> 63) {
+    R = min(ones_up(w1 >> b), 64 - b);  // column xs + 64 is bit b of w1
+    if (R == 64 - b) {
+      const int o = ones_up(w2);
+      R += o;
+      gr = o == 64;
+      right = k + 3;
+    }
+  }
+  while (gl || gr) {
+    uint64_t l[4], r[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      l[i] = gl ? word(left - i) : 0ull;
+      r[i] = gr ? word(right + i) : 0ull;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (gl) {
+        const int o = ones_down(l[i]);
+        L += o;
+        gl = o == 64;
+      }
+      if (gr) {
+        const int o = ones_up(r[i]);
+        R += o;
+        gr = o == 64;
+      }
+    }
+    left -= 4;
+    right += 4;
+    gl &= L < kDirRunCap;
+    gr &= R < kDirRunCap;
+  }
+}
+
+// What a phase of a packet derives from its thread or lane stays within the
+// phase: kept across the packet loop it would spill (64 registers at two
+// workgroups per CU), and a kernel with scratch memory starts 2 us later.
+__device__ __forceinline__ void own(int& i) { asm volatile("" : "+v"(i)); }
+
 // item words and mask records of packet p's slots into LDS (recs: 16 dwords per slot)
-__device__ __forceinline__ int direct_load_packet(const int* cnt, const int32_t* counts, const int32_t* items,
-                                                  int item_cap, const MaskRec* mrec, int p, uint32_t* recs, int* words) {
+__device__ __forceinline__ int direct_load_packet(const int* cnt, const DirLists& li, const int32_t* items, int item_cap,
+                                                  const MaskRec* mrec, int p, uint32_t* recs, int* words) {
   int first = 0, ccount = 0;
   const int cls = direct_packet_class(cnt, p, first, ccount);
   const int ipp = direct_items(cls);
-  if ((int)threadIdx.x < ipp * 16) {
-    const int sl = threadIdx.x >> 4, q = threadIdx.x & 15;
+  int tid = threadIdx.x;
+  own(tid);
+  if (tid < ipp * 16) {
+    const int sl = tid >> 4, q = tid & 15;
     const int k = first + sl;
-    const int word = k < ccount ? class_item(counts, items, item_cap, cls, k) : -1;
+    const int word = k < ccount ? *direct_item_at(li, items, item_cap, cls, k) : -1;
     if (q == 0) words[sl] = word;
     recs[sl * 16 + q] = word >= 0 ? reinterpret_cast<const uint32_t*>(mrec + (word >> kItemStripBits))[q] : 0u;
   }
@@ -781,36 +893,48 @@ __device__ __forceinline__ void direct_strip_sums(int cls, const uint32_t* recs,
 
 typedef unsigned short us2 __attribute__((ext_vector_type(2)));
 typedef short s16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ us2 as_us2(uint32_t x) { return __builtin_bit_cast(us2, x); }
-__device__ __forceinline__ us2 sq2(uint32_t x) { const us2 v = as_us2(x); return v * v; }
-__device__ __forceinline__ int max4(us2 a, us2 b) {
-  const us2 m = __builtin_elementwise_max(a, b);
-  return max((int)m.x, (int)m.y);
+__device__ __forceinline__ us2 max2(us2 a, us2 b) { return __builtin_elementwise_max(a, b); }
+__device__ __forceinline__ us2 min2(us2 a, us2 b) { return __builtin_elementwise_min(a, b); }
+// Largest of three in one instruction (v_pk_maximum3_f16): the patterns of
+// non-negative FP16 numbers, 0 .. 0x7BFF, are ordered as the numbers are, and
+// denormals are kept.  Values up to 31743 only.
+__device__ __forceinline__ us2 max3_f16(us2 a, us2 b, us2 c) {
+  return __builtin_bit_cast(us2, __builtin_elementwise_maximum(
+                                     __builtin_elementwise_maximum(__builtin_bit_cast(f16x2, a), __builtin_bit_cast(f16x2, b)),
+                                     __builtin_bit_cast(f16x2, c)));
 }
+__device__ __forceinline__ us2 splat2(uint32_t x) { return as_us2(x * 0x10001u); }
 
-// PK = 1: items of at most 512 rows.  Every e is then at most 255^2 (rows 0
-// and n - 1 are padding with g = 0, and min(u, n - 1 - u) <= 255), so g is
-// clamped to 255 (a candidate with g >= 255 is >= 255^2 >= e either way: no
-// e changes) and the table holds g^2 (< 2^16).  The search runs in packed
-// 16-bit arithmetic, two rows per instruction: sums saturate at 65535, which
-// is never below the best value (<= 65025).
+// The table of a packet holds H = C - g^2 (16 bits, larger = nearer), so that
+// a candidate of distance d is H - d^2 with the difference kept at 0 from
+// below, and the best of a row is a maximum: C - e.  Three forms:
+// PK = 0: items of at most 256 rows (classes 0-3).  Rows 0 and n - 1 are
+// padding with g = 0 and min(u, n - 1 - u) <= 127, so every e is at most
+// 127^2: g is clamped to 127 (a candidate with g >= 127 is >= 127^2 >= e either
+// way: no e changes) and C = 16384, which the three-way maximum takes.
+// PK = 1: items of 257 to 512 rows (class 4).  Likewise e <= 255^2: g is
+// clamped to 255 and C = 65535.
 // PK = 2: taller items (up to 1152 rows).  Every e is at most 575^2, so g is
-// clamped to 576, and the table holds T(g) = g^2 for g < 255 and
+// clamped to 576, and the table holds C - T(g) with T(g) = g^2 for g < 255 and
 // 255^2 + (g - 255) above (at most 65346, 16 bits; T(g) <= g^2 and T grows
-// with g).  The packed search over T is exact for every row whose e is below
-// 255^2 (each clamped candidate is at least 255^2); a group in which some row
-// ends at 255^2 or above is searched again in exact 32-bit arithmetic,
-// decoding g^2 from T.  Those are the rows more than 254 pixels from the
-// mask's outside, a small share of the tallest items.
-// PK = 0: the table holds g and the search is exact 32-bit (AREA of the
-// taller items).
-// The g table of a packet (PK 1: min(g, 255)^2; PK 2: T(min(g, 576)); PK 0:
-// g; 0 past each slot's item), 16 bits per (row, column), four rows per
-// 64-bit word.
-template <int PK>
+// with g), C = 65535.  The packed search over T is exact for every row whose e
+// is below 255^2 (each clamped candidate is at least 255^2); a row that ends
+// at 255^2 or above has its four-row group searched again in exact 32-bit
+// arithmetic, decoding g^2 from T.  Those are the rows more than 254 pixels
+// from the mask's outside, a small share of the tallest items.
+constexpr int edt_c(int pk) { return pk == 0 ? 16384 : 65535; }
+
+// H of every row of a packet's slots (C past each slot's item), 16 bits per
+// (row, column), four rows per 64-bit word; and the largest entry of every
+// 8-row block (of MC adjacent columns together), m8[block][column / MC].
+template <int PK, int MC>
 __device__ __forceinline__ void direct_table(int cls, const uint32_t* recs, const int* words, uint2* gt_all,
-                                             int lane, int kb) {
+                                             uint16_t* m8, int lane, int kb) {
+  own(lane);
   const int rows_c = class_rows(cls), ipp = direct_items(cls);
+  constexpr int C = edt_c(PK), kClamp = PK == 0 ? 127 : 255;
   const int nbs = rows_c / kBlkRows;  // blocks per slot
   const int nblk = ipp * nbs;         // blocks of the packet
 
@@ -831,14 +955,11 @@ __device__ __forceinline__ void direct_table(int cls, const uint32_t* recs, cons
         const int u = (bl - slot * nbs) * kBlkRows + (lane & 15);
         if (u > 0 && u < n - 1) {
           const uint64_t* mb = reinterpret_cast<const uint64_t*>(((uint64_t)rc[1] << 32) | rc[0]);
-          const int y0 = (int)rc[4], wq = (int)rc[11], fw = (int)rc[12];
+          const int y0 = (int)rc[4], x0 = (int)rc[6], x1 = (int)rc[7], wq = (int)rc[11];
           const int xs = (int)rc[14] + (word & ((1 << kItemStripBits) - 1)) * strip_width((int)rc[9]);
-          const uint64_t* row = mb + (int64_t)(y0 - 1 + u) * wq;
-          const uint64_t win = load_window(row, xs, wq, fw);
-          // the table clamps g at 576 or below: runs past the window's ends
-          // matter up to that length
-          const int L = (win & 1ull) ? run_left(row, xs - 1, wq, fw, kDirRunCap) : 0;
-          const int R = (win >> 63) ? run_right(row, xs + 64, wq, fw, kDirRunCap) : 0;
+          uint64_t win;
+          int L, R;
+          row_window(mb + (int64_t)(y0 - 1 + u) * wq, xs, x0, x1, win, L, R);
           r = make_rowrec(win, L, R);
         }
       }
@@ -852,10 +973,22 @@ __device__ __forceinline__ void direct_table(int cls, const uint32_t* recs, cons
       const bool lane_ok = lane < it.SW;
       uint2* gt = gt_all + ((slot * rows_c + r0) >> 2) * 64 + lane;
       const s16x2 l2 = {(short)lane, (short)lane};
+      us2 high = as_us2(0u);  // largest entries of the 8-row block so far, even and odd rows
+      // after the second word of an 8-row block: its largest entry
+      auto block_done = [&](int k4) {
+        if (!(k4 & 4)) return;
+        uint32_t v = max((uint32_t)high.x, (uint32_t)high.y);
+        if (MC >= 2) v = max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, true));
+        if (MC >= 4) v = max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, true));
+        if (lane % MC == 0) m8[((slot * rows_c + r0 + k4) >> 3) * (64 / MC) + lane / MC] = (uint16_t)v;
+        high = as_us2(0u);
+      };
 #pragma unroll
       for (int k4 = 0; k4 < kBlkRows; k4 += 4) {
         if (r0 + k4 >= it.n - 1) {  // padding rows only
-          gt[(k4 >> 2) * 64] = make_uint2(0u, 0u);
+          gt[(k4 >> 2) * 64] = make_uint2(C * 0x10001u, C * 0x10001u);
+          high = splat2(C);
+          block_done(k4);
           continue;
         }
         uint32_t wd[2];
@@ -873,21 +1006,13 @@ __device__ __forceinline__ void direct_table(int cls, const uint32_t* recs, cons
             const s16x2 a2 = __builtin_bit_cast(s16x2, (w0 & 0xFFFFu) | (w1 << 16));
             const s16x2 b2 = __builtin_bit_cast(s16x2, (w0 >> 16) | (w1 & 0xFFFF0000u));
             const s16x2 zero = {0, 0};
-            s16x2 g = __builtin_elementwise_max(
-                __builtin_elementwise_max(__builtin_elementwise_min(l2 - a1, b1 - l2), __builtin_elementwise_min(l2 - a2, b2 - l2)),
-                zero);
-            if (PK == 1) {
-              const s16x2 cap = {255, 255};
-              const us2 gc = __builtin_bit_cast(us2, __builtin_elementwise_min(g, cap));
-              wd[q] = lane_ok ? __builtin_bit_cast(uint32_t, gc * gc) : 0u;
-            } else if (PK == 2) {
-              const s16x2 cap = {255, 255}, top = {576, 576};
-              const us2 g1 = __builtin_bit_cast(us2, __builtin_elementwise_min(g, top));
-              const us2 gc = __builtin_bit_cast(us2, __builtin_elementwise_min(g, cap));
-              wd[q] = lane_ok ? __builtin_bit_cast(uint32_t, gc * gc + (g1 - gc)) : 0u;
-            } else {
-              wd[q] = lane_ok ? __builtin_bit_cast(uint32_t, g) : 0u;
-            }
+            s16x2 g = __builtin_elementwise_max(__builtin_elementwise_min(l2 - a1, b1 - l2), zero);
+            if (w0 | w1) g = __builtin_elementwise_max(g, __builtin_elementwise_min(l2 - a2, b2 - l2));  // uniform
+            const s16x2 cap = {kClamp, kClamp}, tall = {576, 576};
+            const us2 gc = __builtin_bit_cast(us2, __builtin_elementwise_min(g, cap));
+            us2 sq = gc * gc;
+            if (PK == 2) sq += __builtin_bit_cast(us2, __builtin_elementwise_min(g, tall)) - gc;
+            wd[q] = lane_ok ? __builtin_bit_cast(uint32_t, splat2(C) - sq) : C * 0x10001u;
           } else {
             uint32_t h[2];
 #pragma unroll
@@ -895,141 +1020,238 @@ __device__ __forceinline__ void direct_table(int cls, const uint32_t* recs, cons
               const uint4 ru =
                   make_uint4(__builtin_amdgcn_readlane(r.x, src + e), __builtin_amdgcn_readlane(r.y, src + e),
                              __builtin_amdgcn_readlane(r.z, src + e), __builtin_amdgcn_readlane(r.w, src + e));
-              h[e] = lane_ok ? (uint32_t)g_rec(ru, lane) : 0u;
-              if (PK == 1) h[e] = min(h[e], 255u) * min(h[e], 255u);
-              if (PK == 2) h[e] = min(h[e], 255u) * min(h[e], 255u) + (min(h[e], 576u) - min(h[e], 255u));
+              const uint32_t g = lane_ok ? (uint32_t)g_rec(ru, lane) : 0u, gc = min(g, (uint32_t)kClamp);
+              h[e] = C - gc * gc - (PK == 2 ? min(g, 576u) - gc : 0u);
             }
             wd[q] = h[0] | (h[1] << 16);
           }
         }
         gt[(k4 >> 2) * 64] = make_uint2(wd[0], wd[1]);
+        high = max2(high, max2(as_us2(wd[0]), as_us2(wd[1])));
+        block_done(k4);
       }
+    }
+  }
+}
+
+// Exact 32-bit column search of four rows, whose table word is `base` (one
+// lane per column), for the tall items' rows that the packed search cannot
+// hold: outward from the rows, four distances per step on both sides while any
+// row can still improve.
+__device__ __forceinline__ void search32(const uint2* base, int* best) {
+  auto gsq_of = [](int h) {  // g^2 decoded from C - T
+    const int t = edt_c(2) - h;
+    return t < 65025 ? t : (t - 64770) * (t - 64770);
+  };
+  int bmax = 0;
+  const uint2 w = base[0];
+  const int g4[4] = {(int)(w.x & 0xFFFFu), (int)(w.x >> 16), (int)(w.y & 0xFFFFu), (int)(w.y >> 16)};
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    best[k] = gsq_of(g4[k]);
+    bmax = max(bmax, best[k]);
+  }
+  // d = 1 (mod 4): the windows start on words, up at u0 - d - 3, down at
+  // u0 + d - 1 (one row early)
+  for (int d = 1; d * d < bmax; d += 4) {
+    const uint2* pu = base - ((d + 3) >> 2) * 64;
+    const uint2* pd = base + ((d - 1) >> 2) * 64;
+    int su[8], sd[8];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const uint2 x = pu[q * 64], y = pd[q * 64];
+      su[4 * q] = gsq_of((int)(x.x & 0xFFFFu));
+      su[4 * q + 1] = gsq_of((int)(x.x >> 16));
+      su[4 * q + 2] = gsq_of((int)(x.y & 0xFFFFu));
+      su[4 * q + 3] = gsq_of((int)(x.y >> 16));
+      sd[4 * q] = gsq_of((int)(y.x & 0xFFFFu));
+      sd[4 * q + 1] = gsq_of((int)(y.x >> 16));
+      sd[4 * q + 2] = gsq_of((int)(y.y & 0xFFFFu));
+      sd[4 * q + 3] = gsq_of((int)(y.y >> 16));
+    }
+    bmax = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)  // row u0 + k at distance d + i: up index k - i + 3, down k + i + 1
+        best[k] = min(best[k], (d + i) * (d + i) + min(su[k - i + 3], sd[k + i + 1]));
+      bmax = max(bmax, best[k]);
+    }
+  }
+}
+
+// The candidates at distances d .. d + 7 (d = 1 mod 8) on the sides SIDES (1:
+// above, 2: below, 3: both) of the eight rows B (two rows per register), from
+// the 16 table rows that start at pu (row u0 - d - 7) and pd (row u0 + d - 1).
+// Row u0 + k at distance d + i is entry k - i + 7 above and k + i + 1 below:
+// even entries come as aligned pairs of rows (2j, 2j + 1), odd ones as (2j +
+// 1, 2j + 2).  The squares are the same for every lane: scalar arithmetic, each
+// from the one before (a step starts at d <= 249: only the last can pass 255,
+// and distance 256 may stand as 255, which no row's result can tell: every e
+// below 255^2 is below both, and no e of class 4 is above).  With the three-way
+// maximum, both sides go from the farthest distance inwards, each step in
+// taking off the difference of the squares (17 instructions per pair of rows
+// instead of 24), one side two distances at a time (12 instead of 16).
+template <int SIDES, int PK>
+__device__ __forceinline__ void search_step(const uint2* pu, const uint2* pd, int d, us2 (&B)[4]) {
+  uint32_t U[8], V[8], Uo[7], Vo[7];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    if (SIDES & 1) {
+      const uint2 x = pu[q * 64];
+      U[2 * q] = x.x;
+      U[2 * q + 1] = x.y;
+    }
+    if (SIDES & 2) {
+      const uint2 y = pd[q * 64];
+      V[2 * q] = y.x;
+      V[2 * q + 1] = y.y;
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < 7; ++j) {
+    if (SIDES & 1) Uo[j] = __builtin_amdgcn_alignbyte(U[j + 1], U[j], 2);
+    if (SIDES & 2) Vo[j] = __builtin_amdgcn_alignbyte(V[j + 1], V[j], 2);
+  }
+  us2 D[kDirSteps];  // (d + i)^2 in both halves
+  {
+    uint32_t v = (uint32_t)(d * d) * 0x10001u, up = (uint32_t)(2 * d + 1) * 0x10001u;
+#pragma unroll
+    for (int i = 0; i < kDirSteps; ++i) {
+      D[i] = as_us2(v);
+      v += up;
+      up += 0x20002u;
+    }
+    const uint32_t e = (uint32_t)min(d + kDirSteps - 1, 255);
+    D[kDirSteps - 1] = as_us2(e * e * 0x10001u);
+  }
+  // rows 2q, 2q + 1 at distance d + i
+  auto above = [&](int q, int i) { return as_us2((i & 1) ? U[(2 * q + 7 - i) >> 1] : Uo[(2 * q + 6 - i) >> 1]); };
+  auto below = [&](int q, int i) { return as_us2((i & 1) ? V[(2 * q + i + 1) >> 1] : Vo[(2 * q + i) >> 1]); };
+  auto less = [](us2 a, us2 b) { return __builtin_elementwise_sub_sat(a, b); };
+  if (PK == 0 && SIDES == 3) {
+    us2 t[4];
+#pragma unroll
+    for (int i = kDirSteps - 1; i >= 0; --i) {
+      const us2 off = i > 0 ? splat2((uint32_t)(2 * (d + i) - 1)) : D[0];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        t[q] = i == kDirSteps - 1 ? max2(above(q, i), below(q, i)) : max3_f16(above(q, i), below(q, i), t[q]);
+        t[q] = less(t[q], off);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) B[q] = max2(B[q], t[q]);
+    return;
+  }
+#pragma unroll
+  for (int i = 0; i < kDirSteps; i += 2) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      us2 c0, c1;
+      if (SIDES == 3) {
+        c0 = max2(above(q, i), below(q, i));
+        c1 = max2(above(q, i + 1), below(q, i + 1));
+      } else {
+        c0 = SIDES == 1 ? above(q, i) : below(q, i);
+        c1 = SIDES == 1 ? above(q, i + 1) : below(q, i + 1);
+      }
+      c0 = less(c0, D[i]);
+      c1 = less(c1, D[i + 1]);
+      B[q] = PK == 0 ? max3_f16(B[q], c0, c1) : max2(max2(B[q], c0), c1);
     }
   }
 }
 
 // The squared distances (AREA: 1 inside, 0 outside) of the kDirRows rows of
-// one group, whose first table word is `base` (one lane per column; RS: the
-// table's words per row quad).  Rows are searched together, kDirSteps
-// distances per step: the candidates at distances d .. d + kDirSteps - 1 come
-// from consecutive table rows on each side, and a step runs while any row of
-// the group can still improve (rows that are done are updated with
-// candidates that cannot win).
-template <int SPATIAL, int PK, int RS>
-__device__ __forceinline__ void direct_group(const uint2* base, int* best) {
-  int bmax = 0;
-  // g^2 of a table entry (PK 1: the entry itself, PK 2: decoded from T)
-  auto gsq_of = [](int t) { return PK == 1 ? t : PK == 2 ? (t < 65025 ? t : (t - 64770) * (t - 64770)) : t * t; };
-  // initial values: the rows' own entries, g^2 (exact = false with PK 2:
-  // T itself, for the packed search)
-  auto init_exact = [&](bool exact) {
-    bmax = 0;
+// one group, whose first table word is `base` (one lane per column) and whose
+// 8-row block is blk, the table's blocks being -1 .. last (mins: block 0's
+// entry of this lane, one every 64 / MC).  Rows are searched together, outward,
+// kDirSteps distances at a time, while any row of any lane can still improve.
+// Before a step, the largest entries of the two 8-row blocks that its window
+// on each side meets bound its candidates: a side where no lane's bound can
+// improve any of its rows is skipped.  Inside a large mask most windows hold
+// only rows far from the mask's edge, and half to two thirds of the half steps
+// go (a model of the wavefronts' steps: 117 -> 60 instructions per row and
+// wavefront for 1080p masks, 55 -> 39 for 480p ones, against four rows, four
+// distances and no test).
+//
+// u0: the group's first row, n: the item's rows.  A row's distance to the
+// padding row on the nearer side bounds its result from the start, so that
+// windows that cannot matter are skipped before the search has come across the
+// row's own nearest edge (the bound less one is what the rows start from: the
+// search then finds the exact value, the padding row's at the latest).  Not for
+// the tallest items, whose nearest edge is mostly at the side (2528 us without,
+// 2556 with, at 500 masks of 1920x1080).
+//
+// VALU-bound (62-74 % busy; the rest is the ends of packets, where few
+// wavefronts are left).  Kernel times, four rows and distances at a time without
+// the test / now: 16 frames of 1920x1080 with 500 masks, classes 0-4 1629 /
+// 1326 us, tall items 3159 / 2520 us; 64 frames of 640x480 with 60 masks 257 /
+// 235 us; 8 masks of 336x336 24.9 / 23.1 us.
+template <int SPATIAL, int PK, int MC>
+__device__ __forceinline__ void direct_group(const uint2* base, const uint16_t* mins, int blk, int last, int u0, int n,
+                                             us2 (&E)[4]) {
+  constexpr int C = edt_c(PK);
+  const uint2 w0 = base[0], w1 = base[64];
+  us2 B[4] = {as_us2(w0.x), as_us2(w0.y), as_us2(w1.x), as_us2(w1.y)};
+  if (SPATIAL != 0) {
 #pragma unroll
-    for (int q = 0; q < kDirRows / 4; ++q) {
-      const uint2 w = base[q * RS];
-      const int g4[4] = {(int)(w.x & 0xFFFFu), (int)(w.x >> 16), (int)(w.y & 0xFFFFu), (int)(w.y >> 16)};
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        best[4 * q + k] = SPATIAL != 0 ? (g4[k] > 0 ? 1 : 0) : (PK == 2 && !exact) ? g4[k] : gsq_of(g4[k]);
-        bmax = max(bmax, best[4 * q + k]);
-      }
-    }
-  };
-  // exact 32-bit search.  d = 1 (mod 4): the windows start on words, up
-  // at u0 - d - 3, down at u0 + d - 1 (one row early)
-  auto search32 = [&]() {
-    for (int d = 1; d * d < bmax; d += kDirSteps) {
-      constexpr int NQ = (kDirRows + kDirSteps) / 4;  // words per window
-      const uint2* pu = base - ((d + kDirSteps - 1) >> 2) * RS;
-      const uint2* pd = base + ((d - 1) >> 2) * RS;
-      int su[4 * NQ], sd[4 * NQ];
-#pragma unroll
-      for (int q = 0; q < NQ; ++q) {
-        const uint2 x = pu[q * RS], y = pd[q * RS];
-        const int xa = (int)(x.x & 0xFFFFu), xb = (int)(x.x >> 16), xc = (int)(x.y & 0xFFFFu), xd = (int)(x.y >> 16);
-        const int ya = (int)(y.x & 0xFFFFu), yb = (int)(y.x >> 16), yc = (int)(y.y & 0xFFFFu), yd = (int)(y.y >> 16);
-        su[4 * q] = gsq_of(xa);
-        su[4 * q + 1] = gsq_of(xb);
-        su[4 * q + 2] = gsq_of(xc);
-        su[4 * q + 3] = gsq_of(xd);
-        sd[4 * q] = gsq_of(ya);
-        sd[4 * q + 1] = gsq_of(yb);
-        sd[4 * q + 2] = gsq_of(yc);
-        sd[4 * q + 3] = gsq_of(yd);
-      }
-      bmax = 0;
-#pragma unroll
-      for (int k = 0; k < kDirRows; ++k) {
-#pragma unroll
-        for (int i = 0; i < kDirSteps; ++i)  // row u0 + k at distance d + i: up index k - i + 3, down k + i + 1
-          best[k] = min(best[k], (d + i) * (d + i) + min(su[k - i + kDirSteps - 1], sd[k + i + 1]));
-        bmax = max(bmax, best[k]);
-      }
-    }
-  };
-  init_exact(false);
-  if (SPATIAL == 0 && PK != 0) {
-    // packed: rows (0,1) and (2,3) of the group in one register each;
-    // the window rows as aligned pairs (2j, 2j+1) and odd pairs
-    // (2j+1, 2j+2); the table holds g^2.
-    const int b0v = best[0], b1v = best[1], b2v = best[2], b3v = best[3];
-    us2 B[2] = {as_us2((uint32_t)b0v | ((uint32_t)b1v << 16)), as_us2((uint32_t)b2v | ((uint32_t)b3v << 16))};
-    int pmax = max(max(b0v, b1v), max(b2v, b3v));
-    for (int d = 1; d * d < pmax; d += kDirSteps) {
-      const uint2* pu = base - ((d + kDirSteps - 1) >> 2) * RS;
-      const uint2* pd = base + ((d - 1) >> 2) * RS;
-      const uint2 u0w = pu[0], u1w = pu[RS], d0w = pd[0], d1w = pd[RS];
-      const uint32_t U[4] = {u0w.x, u0w.y, u1w.x, u1w.y};
-      const uint32_t Dn[4] = {d0w.x, d0w.y, d1w.x, d1w.y};
-      uint32_t Uo[3], Do[3];
-#pragma unroll
-      for (int j = 0; j < 3; ++j) {
-        Uo[j] = __builtin_amdgcn_alignbyte(U[j + 1], U[j], 2);
-        Do[j] = __builtin_amdgcn_alignbyte(Dn[j + 1], Dn[j], 2);
-      }
-#pragma unroll
-      for (int i = 0; i < kDirSteps; ++i) {
-        // (d + i)^2 is the same for every lane: scalar arithmetic, one
-        // scalar operand of the packed adds
-        const uint32_t dd = (uint32_t)min((d + i) * (d + i), 65535);
-        const us2 D = as_us2(dd | (dd << 16));
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {  // rows 2q, 2q + 1 at distance d + i
-          const uint32_t up = (i & 1) ? U[(3 + 2 * q - i) >> 1] : Uo[(2 + 2 * q - i) >> 1];
-          const uint32_t dn = (i & 1) ? Dn[(1 + 2 * q + i) >> 1] : Do[(2 * q + i) >> 1];
-          B[q] = __builtin_elementwise_min(
-              B[q], __builtin_elementwise_add_sat(__builtin_elementwise_min(as_us2(up), as_us2(dn)), D));
-        }
-      }
-      pmax = max4(B[0], B[1]);
-    }
-    best[0] = B[0].x;
-    best[1] = B[0].y;
-    best[2] = B[1].x;
-    best[3] = B[1].y;
-    if (PK == 2 && max(max(best[0], best[1]), max(best[2], best[3])) >= 65025) {
-      // some row of the group is at least 255 from the outside: exact search
-      init_exact(true);
-      search32();
-    }
-  } else if (SPATIAL == 0) {
-    search32();
+    for (int q = 0; q < 4; ++q) E[q] = min2(splat2(C) - B[q], splat2(1));
+    return;
   }
+  if (PK != 2) {
+    const bool top = u0 + 3 < n - u0 - 4;  // the nearer padding row is row 0
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int a = top ? u0 + 2 * q : n - 1 - u0 - 2 * q, b = top ? a + 1 : a - 1;  // rows' distances to it (rows past the item: of no matter)
+      const uint32_t x = (uint32_t)max(C - 1 - a * a, 0), y = (uint32_t)max(C - 1 - b * b, 0);
+      B[q] = max2(B[q], as_us2(x | (y << 16)));
+    }
+  }
+  // the smallest of the eight rows, in both halves
+  auto smallest = [&]() {
+    const us2 m = min2(min2(B[0], B[1]), min2(B[2], B[3]));
+    return min2(m, __builtin_shufflevector(m, m, 1, 0));
+  };
+  // block entries of step j: the farther block above (low half) and below
+  auto ends = [&](int j) {
+    const int a = max(blk - j - 1, -1), b = min(blk + j + 1, last);
+    return (uint32_t)mins[a * (64 / MC)] | ((uint32_t)mins[b * (64 / MC)] << 16);
+  };
+  us2 worst = smallest();
+  uint32_t near = (uint32_t)mins[blk * (64 / MC)] * 0x10001u, far = ends(0);
+  // no candidate at d with d^2 >= C can improve a row
+  for (int j = 0; (8 * j + 1) * (8 * j + 1) < C; ++j) {
+    const int d = 8 * j + 1;
+    const uint32_t dd = (uint32_t)(d * d);
+    if (__ballot((int)worst.x < C - (int)dd) == 0) break;
+    const uint32_t next = ends(j + 1);
+    const us2 bound = __builtin_elementwise_sub_sat(max2(as_us2(near), as_us2(far)), splat2(dd));
+    const uint32_t gain = __builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(bound, worst));
+    near = far;
+    far = next;
+    const bool up = __ballot((gain & 0xFFFFu) != 0) != 0, down = __ballot((gain >> 16) != 0) != 0;
+    const uint2* pu = base - 2 * (j + 1) * 64;
+    const uint2* pd = base + 2 * j * 64;
+    if (up && down) search_step<3, PK>(pu, pd, d, B);
+    else if (up) search_step<1, PK>(pu, pd, d, B);
+    else if (down) search_step<2, PK>(pu, pd, d, B);
+    else continue;
+    worst = smallest();
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) E[q] = splat2(C) - B[q];
 }
 
-template <int SPATIAL, bool WE, int PK>
+template <int SPATIAL, bool WE, int PK, int MC>
 __device__ __forceinline__ void direct_packet(int cls, int s, int S, const uint32_t* recs, const int* words,
-                                              uint2* gt_all, float* part, int lane, int kb, int32_t* e_out,
-                                              int32_t* queue, int nb, int& next) {
+                                              uint2* gt_all, uint16_t* m8, float* part, int lane, int kb,
+                                              int32_t* e_out) {
+  own(lane);
   const int rows_c = class_rows(cls), ipp = direct_items(cls);
   const int nbs = rows_c / kBlkRows;  // blocks per slot
   const int nblk = ipp * nbs;         // blocks of the packet
-
-  direct_table<PK>(cls, recs, words, gt_all, lane, kb);
-  __syncthreads();
-  // the workgroup's next packet (no barrier waits for this atomic before the
-  // packet's end)
-  if (queue && threadIdx.x == 0) next = nb + atomicAdd(queue, 1);
 
   // ---- search: this workgroup's blocks (every S-th from s), one wavefront
   // per block in a stride, kDirRows rows at a time (direct_group); each
@@ -1047,12 +1269,23 @@ __device__ __forceinline__ void direct_packet(int cls, int s, int S, const uint3
     int pr_next = (pr + 1) * P - (y0 - 1);  // first row of the next patch row
     float acc = 0.f;
     const uint2* tb = gt_all + ((slot * rows_c + b0) >> 2) * 64 + lane;  // the block's first word
-#pragma unroll
+#pragma unroll 1
     for (int gi = 0; gi < kBlkRows; gi += kDirRows) {
       if (b0 + gi >= ub) break;
       const uint2* base = tb + (gi >> 2) * 64;  // row u0 = b0 + gi
+      us2 E[kDirRows / 2];
+      direct_group<SPATIAL, PK, MC>(base, m8 + lane / MC, (slot * rows_c + b0 + gi) >> 3,
+                                    nblk * (kBlkRows / 8) + kDirBottom / 8 - 1, b0 + gi, n, E);
       int best[kDirRows];
-      direct_group<SPATIAL, PK, 64>(base, best);
+#pragma unroll
+      for (int q = 0; q < kDirRows / 2; ++q) {
+        best[2 * q] = E[q].x;
+        best[2 * q + 1] = E[q].y;
+      }
+      if (SPATIAL == 0 && PK == 2) {  // rows at least 255 from the outside: exact search
+        if (max(max(best[0], best[1]), max(best[2], best[3])) >= 65025) search32(base, best);
+        if (max(max(best[4], best[5]), max(best[6], best[7])) >= 65025) search32(base + 64, best + 4);
+      }
 #pragma unroll
       for (int k = 0; k < kDirRows; ++k) {
         const int u = b0 + gi + k;
@@ -1071,7 +1304,6 @@ __device__ __forceinline__ void direct_packet(int cls, int s, int S, const uint3
     }
     flush_patch_part(bpart, lane, lane_ok, P, y0, lb, pr, acc);
   }
-  __syncthreads();
 }
 
 // ROWS: table rows of one workgroup (512: classes 0-4, 1152: class 5)
@@ -1079,15 +1311,23 @@ template <int SPATIAL, bool WE, int ROWS>
 __global__ __launch_bounds__(kEdtWaves * 64) __attribute__((amdgpu_waves_per_eu(ROWS > 512 ? 4 : 8))) void k_edt_direct(
     int32_t* __restrict__ counts, const int32_t* __restrict__ items, int item_cap,
     const MaskRec* __restrict__ mrec, int32_t* e_out, float* gpart) {
-  __shared__ uint2 gt_all[(ROWS + 2 * kDirGuard) / 4 * 64];  // g table, 4 rows per word; zero guard rows at each end
-  __shared__ float part_all[kEdtBlocks * kEdtPartRows * 8];
+  // Two workgroups of 512 rows share a CU's 160 KB; with 1152 rows the block
+  // minima of four columns are kept together so that one fits.
+  constexpr int MC = ROWS > 512 ? 4 : 1;
+  constexpr int kTable = (ROWS + kDirTop + kDirBottom) / 4 * 64, kMins = (ROWS + kDirTop + kDirBottom) / 8 * (64 / MC);
+  __shared__ uint2 gt_all[kTable];    // g table, 4 rows per word; zero guard rows at each end
+  __shared__ uint16_t m8_all[kMins];  // largest entry of each 8-row block
+  __shared__ float part_all[ROWS / kBlkRows * kEdtPartRows * 8];
   __shared__ uint32_t recs[kEdtWaves * 16];
   __shared__ int words[kEdtWaves];
+  __shared__ DirLists lists;
   __shared__ int taken;
   const int lane = threadIdx.x & 63, kb = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  for (int i = threadIdx.x; i < (ROWS + 2 * kDirGuard) / 4 * 64; i += kEdtWaves * 64) gt_all[i] = make_uint2(0u, 0u);
+  for (int i = threadIdx.x; i < kTable; i += kEdtWaves * 64) gt_all[i] = make_uint2(0u, 0u);
+  for (int i = threadIdx.x; i < kMins; i += kEdtWaves * 64) m8_all[i] = 0;
+  direct_lists(counts, item_cap, lists);
   int cnt[kClasses];
-  const int total = direct_count(counts, item_cap, ROWS > 512, cnt);
+  const int total = direct_count(lists, ROWS > 512, cnt);
   const int S = direct_split(ROWS > 512, total, gridDim.x);
   // Virtual packets (packet, share) in chunks of kXcds: chunk c belongs to
   // XCD c % kXcds.  The XCD's nb workgroups take its first nb packets one
@@ -1104,15 +1344,27 @@ __global__ __launch_bounds__(kEdtWaves * 64) __attribute__((amdgpu_waves_per_eu(
   // no queue when the XCD's list ends within its first nb packets
   const bool queued = (by_xcd ? kXcds * (x + kXcds * (nb / kXcds)) + nb % kXcds : nb) < N;
   int32_t* queue = queued ? counts + kDirQueue + (ROWS > 512 ? kXcds : 0) + x : nullptr;
-  int next = N;  // past every list (by_xcd: t >= N gives vp >= N)
+  int next = N;  // place of the workgroup's next packet, in thread 0
   for (int t = by_xcd ? blockIdx.x / kXcds : blockIdx.x;;) {
     const int vp = by_xcd ? kXcds * (x + kXcds * (t / kXcds)) + t % kXcds : t;
     if (vp >= N) break;  // the XCD's list is in increasing order: nothing after it either
-    const int p = vp / S, s = vp - p * S;
-    const int cls = direct_load_packet(cnt, counts, items, item_cap, mrec, p, recs, words);
+    const int p = vp / S, sh = vp - p * S;
+    const int cls = direct_load_packet(cnt, lists, items, item_cap, mrec, p, recs, words);
     float* part = S == 1 ? part_all : gpart + (int64_t)p * kDirPartFloats;
-    direct_packet<SPATIAL, WE, (ROWS <= 512 ? 1 : SPATIAL == 0 ? 2 : 0)>(cls, s, S, recs, words, gt_all + kDirGuard / 4 * 64, part, lane, kb, e_out,
-                                                                         queue, nb, next);
+    uint2* gt = gt_all + kDirTop / 4 * 64;
+    uint16_t* m8 = m8_all + kDirTop / 8 * (64 / MC);
+    auto run = [&](auto pk) {
+      constexpr int PK = decltype(pk)::value;
+      direct_table<PK, MC>(cls, recs, words, gt, m8, lane, kb);
+      __syncthreads();
+      // the workgroup's next packet (no barrier waits for this atomic before the packet's end)
+      if (queue && threadIdx.x == 0) next = nb + atomicAdd(queue, 1);
+      direct_packet<SPATIAL, WE, PK, MC>(cls, sh, S, recs, words, gt, m8, part, lane, kb, e_out);
+    };
+    if (ROWS > 512) run(std::integral_constant<int, 2>{});
+    else if (cls == 4) run(std::integral_constant<int, 1>{});
+    else run(std::integral_constant<int, 0>{});
+    __syncthreads();
     if (S == 1) {
       direct_strip_sums(cls, recs, words, part_all, lane, kb);
       __syncthreads();
@@ -1153,12 +1405,14 @@ __global__ __launch_bounds__(kEdtWaves * 64) void k_edt_dsums(Batch b, const int
     __shared__ int owsum[4];
     for (int f = blockIdx.x; f < b.dyn[0]; f += gridDim.x) pool_order_frame(b, wk, f, ocnt, owsum);
   }
+  __shared__ DirLists lists;
   const int lane = threadIdx.x & 63, kb = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  direct_lists(counts, item_cap, lists);
   int cnt[kClasses];
-  const int total = direct_count(counts, item_cap, false, cnt);
+  const int total = direct_count(lists, false, cnt);
   if (direct_split(false, total, direct_grid) == 1) return;
   for (int p = blockIdx.x; p < total; p += gridDim.x) {
-    const int cls = direct_load_packet(cnt, counts, items, item_cap, mrec, p, recs, words);
+    const int cls = direct_load_packet(cnt, lists, items, item_cap, mrec, p, recs, words);
     direct_strip_sums(cls, recs, words, gpart + (int64_t)p * kDirPartFloats, lane, kb);
     __syncthreads();
   }
