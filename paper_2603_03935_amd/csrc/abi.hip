@@ -1011,10 +1011,8 @@ disc_status disc_query_heatmap(const disc_tokens* tokens, const disc_proj* proj,
   float* D = reinterpret_cast<float*>(x + yb);
   float* fac = reinterpret_cast<float*>(x + yb + gb);
   float* inv_text = reinterpret_cast<float*>(x + yb + 2 * gb);
-  launch_token_stats(b, w, G, cx.st);
-  launch_d_from_r(w.r, G, eps, D, cx.st);
-  launch_heatmap(tokens->data, tokens->dtype, tokens->scale, G, C, proj->data, proj->dtype == DISC_BF16, E, text,
-                 text_dtype == DISC_BF16, q, D, Y, fac, inv_text, heat, cx.st);
+  launch_heatmap(b, w, tokens->data, tokens->scale, G, proj->data, proj->dtype == DISC_BF16, E, text,
+                 text_dtype == DISC_BF16, q, eps, D, Y, fac, inv_text, heat, cx.st);
   if ((st = check_launch(who))) return st;
   return ok();
 }

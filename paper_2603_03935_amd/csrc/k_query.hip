@@ -28,17 +28,22 @@ __device__ __forceinline__ float4 load_row4(const void* base, int64_t off) {
   return *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(base) + off);
 }
 
+// a row's squared norm is summed by 64 lanes, lane l taking elements 4 l .. 4 l
+// + 3 of every 256, in this form, then over the lanes by xor shuffles
+__device__ __forceinline__ float sq4(float4 v) { return v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w; }
+
+__device__ __forceinline__ float inv_norm(float a) { return a > 0.f ? 1.0f / __builtin_sqrtf(a) : 0.f; }
+
 // inv[r] = 1 / ||row r|| (0 for a zero row); one wavefront per row
 template <int BF16>
 __device__ __forceinline__ void invnorm_row(const void* x, int64_t r, int e, float* inv) {
   const int lane = threadIdx.x & 63;
   float a = 0.f;
   for (int c = lane * 4; c < e; c += 256) {
-    const float4 v = load_row4<BF16>(x, r * e + c);
-    a += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+    a += sq4(load_row4<BF16>(x, r * e + c));
   }
   for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o);
-  if (lane == 0) inv[r] = a > 0.f ? 1.0f / __builtin_sqrtf(a) : 0.f;
+  if (lane == 0) inv[r] = inv_norm(a);
 }
 
 // rows 0 .. m - 1 of the result: emb; rows m .. m + q - 1: text
@@ -69,7 +74,13 @@ __global__ __launch_bounds__(256) void k_invnorms(const float* emb, int m, const
 // of four consecutive MFMAs together), so an operand of four MFMAs is one
 // 16-byte LDS read; the row stride BK + 4 keeps those reads free of bank
 // conflicts.
-template <int MT, int WA, int WB, int BK>
+//
+// NORM: the squared norms of the tile's rows of A and B come with the loads
+// (na, nb; valid in every lane of a row's 16 after the run), summed in the
+// order of invnorm_row: a lane of it is one thread and one of four steps.
+// KMB: B is stored with the rows' elements k apart (element k of row n at [k][n]):
+// load_b(row, k) gives element k of rows row .. row + 3.
+template <int MT, int WA, int WB, int BK, bool NORM = false, bool KMB = false>
 struct GemmTile {
   static constexpr int KG = MT == 32 ? 2 : 4;  // K of one MFMA
   static constexpr int TA = MT * WA, TB = MT * WB, LD = BK + 4;
@@ -78,8 +89,12 @@ struct GemmTile {
   static_assert(WA * WB == 4 && QA * 1024 == TA * BK && QB * 1024 == TB * BK && NG % 2 == 0, "tile");
   typedef typename std::conditional<MT == 32, floatx16, floatx4>::type Acc;
   static constexpr int NV = MT * MT / 64;
+  static_assert(!NORM || (BK == 64 && !KMB), "a row's 16 threads and four steps are invnorm_row's 64 lanes");
   alignas(16) float as[2][TA][LD];
   alignas(16) float bs[2][TB][LD];
+  struct Norms {
+    float a[NORM ? QA : 1], b[NORM ? QB : 1];
+  };
 
   // rows of A and B (within the workgroup's tile) of accumulator element v of this lane
   static __device__ __forceinline__ int row_a(int v) {
@@ -101,16 +116,41 @@ struct GemmTile {
     }
   }
 
+  // place of element k
+  static __device__ __forceinline__ int place(int k) {
+    return MT == 32 ? (k & ~7) + ((k >> 1) & 3) + 4 * (k & 1) : (k & ~15) + ((k >> 2) & 3) + 4 * (k & 3);
+  }
+
   // sum over k < e of A[row_a] B[row_b]; load_a(row, k) and load_b(row, k)
   // give elements k .. k + 3 of a row of the tile (k % 4 == 0, below e)
   template <class LA, class LB>
-  __device__ __forceinline__ Acc run(int e, LA load_a, LB load_b) {
+  __device__ __forceinline__ Acc run(int e, LA load_a, LB load_b, Norms* norms = nullptr) {
     const int tid = threadIdx.x, lane = tid & 63;
     // whole vectors, so that the loads write them in place; 256 threads cover
     // 1024 / BK rows a round, so a thread's k is the same in each
     floatx4 ra[QA], rb[QB];
     constexpr int RR = 1024 / BK;
     const int kt = 4 * (tid % (BK / 4)), rt = tid / (BK / 4);
+    // KMB: thread's element k and rows of load i
+    auto kk = [&](int i) { return (tid + 256 * i) / (TB / 4); };
+    auto kn = [&](int i) { return 4 * ((tid + 256 * i) % (TB / 4)); };
+    float sa[NORM ? QA : 1][4], sb[NORM ? QB : 1][4];
+    if (NORM) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+#pragma unroll
+        for (int i = 0; i < QA; ++i) sa[i][j] = 0.f;
+#pragma unroll
+        for (int i = 0; i < QB; ++i) sb[i][j] = 0.f;
+      }
+    }
+    auto add_sq = [](float (&s)[4], floatx4 v) {  // the step's part; the four parts move on by one
+      const float t = s[0] + sq4(make_float4(v.x, v.y, v.z, v.w));
+      s[0] = s[1];
+      s[1] = s[2];
+      s[2] = s[3];
+      s[3] = t;
+    };
     auto fetch = [&](int k0) {  // past the end: the last elements again
       const int k = min(k0 + kt, e - 4);
 #pragma unroll
@@ -120,7 +160,7 @@ struct GemmTile {
       }
 #pragma unroll
       for (int i = 0; i < QB; ++i) {
-        const float4 v = load_b(rt + i * RR, k);
+        const float4 v = KMB ? load_b(kn(i), min(k0 + kk(i), e - 1)) : load_b(rt + i * RR, k);
         rb[i] = floatx4{v.x, v.y, v.z, v.w};
       }
     };
@@ -138,14 +178,27 @@ struct GemmTile {
 #pragma unroll
         for (int i = 0; i < QA; ++i) ra[i] = k0 + kt < e ? ra[i] : zero;
 #pragma unroll
-        for (int i = 0; i < QB; ++i) rb[i] = k0 + kt < e ? rb[i] : zero;
+        for (int i = 0; i < QB; ++i) rb[i] = k0 + (KMB ? kk(i) : kt) < e ? rb[i] : zero;
+      }
+      if (NORM) {
+#pragma unroll
+        for (int i = 0; i < QA; ++i) add_sq(sa[i], ra[i]);
+#pragma unroll
+        for (int i = 0; i < QB; ++i) add_sq(sb[i], rb[i]);
       }
       float* pa = as[buf][rt] + slot(kt);
       float* pb = bs[buf][rt] + slot(kt);
 #pragma unroll
       for (int i = 0; i < QA; ++i) put(pa + i * RR * LD, ra[i]);
 #pragma unroll
-      for (int i = 0; i < QB; ++i) put(pb + i * RR * LD, rb[i]);
+      for (int i = 0; i < QB; ++i) {
+        if (KMB) {
+          float* q = bs[buf][kn(i)] + place(kk(i));
+          q[0] = rb[i].x; q[LD] = rb[i].y; q[2 * LD] = rb[i].z; q[3 * LD] = rb[i].w;
+        } else {
+          put(pb + i * RR * LD, rb[i]);
+        }
+      }
     };
     fetch(0);
     store(0, 0);
@@ -183,28 +236,84 @@ struct GemmTile {
         __builtin_amdgcn_sched_barrier(0);
       }
     }
+    if (NORM) {  // parts j and j + 2, then j and j + 1 (lanes 32 and 16 apart there), then the row's 16 threads
+      auto total = [](const float (&s)[4]) {
+        float a = (s[0] + s[2]) + (s[1] + s[3]);
+        for (int o = 8; o > 0; o >>= 1) a += __shfl_xor(a, o);
+        return a;
+      };
+#pragma unroll
+      for (int i = 0; i < QA; ++i) norms->a[i] = total(sa[i]);
+#pragma unroll
+      for (int i = 0; i < QB; ++i) norms->b[i] = total(sb[i]);
+    }
     return acc;
   }
 };
 
-// sim[j][i] = (text_j . emb_i) inv_emb[i] inv_text[j].  The workgroups of one
-// XCD take consecutive tiles, query tiles first, so that a tile of instances
-// is read from HBM by one XCD.
-template <int BF16, int MT, int WA, int WB, int BK>
+// sum(r) as k_d_from_r adds it (thread t of 1024 every 1024th element, xor
+// shuffles, the 16 wavefronts in order), by 256 threads
+__device__ float sum_1024(const float* r, int n, float* red) {
+  const int tid = threadIdx.x;
+  float a[4] = {0.f, 0.f, 0.f, 0.f};
+  for (int p = tid; p < n; p += 1024) {
+    float v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = r[min(p + 256 * j, n - 1)];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) a[j] += p + 256 * j < n ? v[j] : 0.f;
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    for (int o = 32; o > 0; o >>= 1) a[j] += __shfl_xor(a[j], o);
+    if ((tid & 63) == 0) red[4 * j + (tid >> 6)] = a[j];
+  }
+  __syncthreads();
+  float t = 0.f;
+  for (int i = 0; i < 16; ++i) t += red[i];
+  return t;
+}
+
+// sim[j][i] = (text_j . emb_i) f_i inv_text[j].  SCALE 0: f (inv_emb) and
+// inv_text are given; 1: both are the inverse norms, taken from the rows as
+// they are loaded (one launch and one reading of emb less: the whole call for 5
+// queries over 20011 x 768 33 -> 24 us); 2: likewise, and f_i = D_i / ||emb_i|| with D of Eq. (1) from the
+// m residuals r.  The workgroups of one XCD take consecutive tiles, query tiles
+// first, so that a tile of instances is read from HBM by one XCD.
+template <int BF16, int MT, int WA, int WB, int BK, int SCALE>
 __global__ __launch_bounds__(256) void k_sim(const float* emb, int m, const void* text, int q, int e,
-                                             const float* inv_emb, const float* inv_text, float* sim, int qt) {
-  typedef GemmTile<MT, WA, WB, BK> Tile;
+                                             const float* inv_emb, const float* inv_text, const float* r, float eps,
+                                             float* sim, int qt) {
+  typedef GemmTile<MT, WA, WB, BK, SCALE != 0> Tile;
   __shared__ Tile tile;
+  __shared__ float fa[SCALE ? Tile::TA : 1], fb[SCALE ? Tile::TB : 1], red[16];
   const int b = xcd_remap(blockIdx.x, gridDim.x);
   const int q0 = b % qt * Tile::TA, i0 = b / qt * Tile::TB;
+  float denom = 0.f;
+  if (SCALE == 2) denom = sum_1024(r, m, red) / (float)m + eps;
+  typename Tile::Norms nn;
   const typename Tile::Acc acc =
-      tile.run(e, [&](int r, int k) { return load_row4<BF16>(text, (int64_t)min(q0 + r, q - 1) * e + k); },
-               [&](int r, int k) { return load_row4<0>(emb, (int64_t)min(i0 + r, m - 1) * e + k); });
+      tile.run(e, [&](int x, int k) { return load_row4<BF16>(text, (int64_t)min(q0 + x, q - 1) * e + k); },
+               [&](int x, int k) { return load_row4<0>(emb, (int64_t)min(i0 + x, m - 1) * e + k); }, &nn);
+  if (SCALE) {
+    if (threadIdx.x % 16 == 0) {
+      const int x = threadIdx.x / 16;
+#pragma unroll
+      for (int i = 0; i < Tile::QA; ++i) fa[x + 16 * i] = inv_norm(nn.a[i]);
+#pragma unroll
+      for (int i = 0; i < Tile::QB; ++i) {
+        const float a = nn.b[i];
+        if (SCALE == 1) fb[x + 16 * i] = inv_norm(a);
+        else fb[x + 16 * i] = a > 0.f ? r[min(i0 + x + 16 * i, m - 1)] / denom / __builtin_sqrtf(a) : 0.f;
+      }
+    }
+    __syncthreads();
+  }
   const int i = i0 + Tile::row_b();
-  const float yi = inv_emb[min(i, m - 1)];
+  const float yi = SCALE ? fb[Tile::row_b()] : inv_emb[min(i, m - 1)];
   float tj[Tile::NV];  // all loads before the first store
 #pragma unroll
-  for (int v = 0; v < Tile::NV; ++v) tj[v] = inv_text[min(q0 + Tile::row_a(v), q - 1)];
+  for (int v = 0; v < Tile::NV; ++v) tj[v] = SCALE ? fa[Tile::row_a(v)] : inv_text[min(q0 + Tile::row_a(v), q - 1)];
 #pragma unroll
   for (int v = 0; v < Tile::NV; ++v) {
     const int j = q0 + Tile::row_a(v);
@@ -213,25 +322,28 @@ __global__ __launch_bounds__(256) void k_sim(const float* emb, int m, const void
 }
 
 // Tile by size (us of the whole query call at width 768 or 1024, 16 x 64 / 32
-// x 32 / 64 x 64; the 64 x 64 kernel before, K step 16 and two barriers a
-// step, took 182 us for 1024 x 8000 alone, now 145):
+// x 32 / 64 x 64, all with separate norms; the 64 x 64 kernel before, K step 16
+// and two barriers a step, took 182 us for 1024 x 8000 alone, now 145):
 //   q x m          5 x 20011   16 x 5000   64 x 3000   512 x 3000   1024 x 3000   1024 x 8000
 //                  31/34/49    20/19/32    17/17/25    49/45/49     94/87/76      210/189/165
 // Few queries are bound by reading the instances: the fewer of a tile's query
 // rows are padding, the better.  The larger tile reads less through LDS per
 // product but has a quarter of the workgroups and four times the chain of
 // dependent MFMAs: it wins from about two tiles per CU on.
-template <int BF16>
+static int64_t sim_tiles(int q, int m, int ta, int tb) { return (int64_t)((q + ta - 1) / ta) * ((m + tb - 1) / tb); }
+static bool sim_takes_norms(int q, int m) { return q <= 16 || sim_tiles(q, m, 64, 64) < 512; }
+
+// SCALE as k_sim's (0: inv_emb and inv_text are given; they are unless sim_takes_norms)
+template <int BF16, int SCALE>
 static void launch_sim(const float* emb, int m, const void* text, int q, int e, const float* inv_emb,
-                       const float* inv_text, float* sim, hipStream_t st) {
-  auto tiles = [&](int ta, int tb) { return (int64_t)((q + ta - 1) / ta) * ((m + tb - 1) / tb); };
+                       const float* inv_text, const float* r, float eps, float* sim, hipStream_t st) {
   auto go = [&](auto kernel, int ta, int tb) {
-    hipLaunchKernelGGL(kernel, dim3((unsigned)tiles(ta, tb)), dim3(256), 0, st, emb, m, text, q, e, inv_emb, inv_text, sim,
-                       (q + ta - 1) / ta);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)sim_tiles(q, m, ta, tb)), dim3(256), 0, st, emb, m, text, q, e, inv_emb,
+                       inv_text, r, eps, sim, (q + ta - 1) / ta);
   };
-  if (q <= 16) go(k_sim<BF16, 16, 1, 4, 64>, 16, 64);
-  else if (tiles(64, 64) < 512) go(k_sim<BF16, 16, 2, 2, 64>, 32, 32);
-  else go(k_sim<BF16, 32, 2, 2, 32>, 64, 64);
+  if constexpr (SCALE == 0) go(k_sim<BF16, 32, 2, 2, 32, 0>, 64, 64);
+  else if (q <= 16) go(k_sim<BF16, 16, 1, 4, 64, SCALE>, 16, 64);
+  else go(k_sim<BF16, 16, 2, 2, 64, SCALE>, 32, 32);
 }
 
 // Order-preserving 64-bit key: larger score first, then smaller index.
@@ -432,8 +544,8 @@ static void launch_topk(const float* sim, int m, int q, int k, uint64_t* ka, uin
 // Weighted similarity heat-map of text queries over one frame's patches
 // (Sec. III-C, the feature-similarity figure):
 //   heat[j][p] = D_p cos(text_j, y_p),  y_p = f_p^T P,
-// D of Eq. (1).  The patch tokens are projected by one FP32-MFMA contraction
-// (G x E, K = C); each projected row's inverse norm is folded with D_p into
+// D of Eq. (1).  The patch tokens are projected by one contraction (G x E, K
+// = C) with FP32 sums; each projected row's inverse norm is folded with D_p into
 // one per-patch factor, and the cosine contraction above (k_sim) applies it.
 // ---------------------------------------------------------------------------
 template <int TOK>
@@ -448,39 +560,146 @@ __device__ __forceinline__ float4 load_tok4(const void* base, const float* scale
   return make_float4(x.x * sc, x.y * sc, x.z * sc, x.w * sc);
 }
 
-// Y[G][E] = tokens[G][C] P[C][E]: 64 x 64 tiles (4 wavefronts of 32 x 32),
-// K in steps of 16 through LDS; TOK 0 F32, 1 BF16, 2 FP8 + scale; PB: P in BF16.
+// Y[G][E] = tokens[G][C] P[C][E] in FP32 MFMA; TOK 0 F32, 1 BF16, 2 FP8 +
+// scale; PB: P in BF16.  The first nchunk workgroups add up the tokens' channel
+// sums (colsum_chunk) beside the contraction, which does not need them.  Bound
+// by the FP32 matrix rate (whole call, before / now: 30 x 40 x 1024 x 768 100 / 55
+// us, 78 x 138 x 1280 x 1024 with 64 queries 403 / 312; tiles of 32 x 32 took 58
+// and 372).
 template <int TOK, int PB>
-__global__ __launch_bounds__(256) void k_tokproj(const void* tok, const float* scale, int G, int C, const void* P,
-                                                 int E, float* Y) {
-  constexpr int BK = 16;
-  const int g0 = blockIdx.x * 64, n0 = blockIdx.y * 64;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, wg = wv >> 1, wn = wv & 1;
-  __shared__ float As[64][BK + 1];
-  __shared__ float Bs[64][BK + 1];
-  floatx16 acc = {};
-  const int lr = tid >> 2, lk = (tid & 3) * 4;         // A: row lr, channels lk..lk+3
-  const int bk = tid >> 4, bn = (tid & 15) * 4;        // B: channel bk, columns bn..bn+3
-  for (int k0 = 0; k0 < C; k0 += BK) {
-    const float4 av = g0 + lr < G ? load_tok4<TOK>(tok, scale, g0 + lr, k0 + lk, C) : make_float4(0.f, 0.f, 0.f, 0.f);
-    const float4 bv = load_row4<PB>(P, (int64_t)(k0 + bk) * E + n0 + bn);
-    __syncthreads();
-    As[lr][lk] = av.x; As[lr][lk + 1] = av.y; As[lr][lk + 2] = av.z; As[lr][lk + 3] = av.w;
-    Bs[bn][bk] = bv.x; Bs[bn + 1][bk] = bv.y; Bs[bn + 2][bk] = bv.z; Bs[bn + 3][bk] = bv.w;
-    __syncthreads();
+__global__ __launch_bounds__(256) void k_tokproj(Batch b, Work wk, int nchunk, const void* tok, const float* scale,
+                                                 int G, int C, const void* P, int E, float* Y) {
+  if ((int)blockIdx.x < nchunk) {
+    colsum_chunk<TOK>(b, wk, 0, blockIdx.x);
+    return;
+  }
+  typedef GemmTile<32, 2, 2, 32, false, true> Tile;
+  __shared__ Tile tile;
+  const int t = xcd_remap(blockIdx.x - nchunk, gridDim.x - nchunk), nt = E / Tile::TB;
+  const int g0 = t / nt * Tile::TA, n0 = t % nt * Tile::TB;
+  const typename Tile::Acc acc =
+      tile.run(C, [&](int x, int k) { return load_tok4<TOK>(tok, scale, min(g0 + x, G - 1), k, C); },
+               [&](int n, int k) { return load_row4<PB>(P, (int64_t)k * E + n0 + n); });
 #pragma unroll
-    for (int kk = 0; kk < BK; kk += 2) {
-      const float a = As[32 * wg + (lane & 31)][kk + (lane >> 5)];
-      const float b = Bs[32 * wn + (lane & 31)][kk + (lane >> 5)];
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, acc, 0, 0, 0);
+  for (int v = 0; v < Tile::NV; ++v) {
+    const int g = g0 + Tile::row_a(v);
+    if (g < G) Y[(int64_t)g * E + n0 + Tile::row_b()] = acc[v];
+  }
+}
+
+// The same for BF16 or FP8 tokens and a BF16 P on BF16 MFMA: the products are
+// exact in FP32 either way (an e4m3 code is exact in BF16), the sums are FP32,
+// and a token's scale is applied to its finished row, one rounding instead of
+// one per product (error
+// of the heat-map against 64 bits, rms: 1.9e-8 for either token type, 2.0e-8 and
+// 2.8e-8 on FP32 MFMA).
+// Tiles of 64 WM x 64, four wavefronts of 32 WM x 32, K in steps of 64 through
+// two LDS buffers.  Bound by the latency of the loads when the tiles are few
+// (1200 tokens: 228 workgroups, 16 steps each), so four steps are in flight
+// in registers: 12 us for 1200 x 1024 x 768 with the channel sums beside it,
+// 52 + 6 in FP32 tiles that loaded, stored and waited in turn.  P's rows run along n, its operand along k: a thread loads
+// four k of four n and turns the block over in registers; a wavefront takes 8
+// such blocks along n and 8 along k, whose 8-byte stores meet all banks.
+constexpr int kProjDepth = 4;
+template <int TOK, int WM>
+__global__ __launch_bounds__(256) void k_tokproj16(Batch b, Work wk, int nchunk, const void* tok, const float* scale,
+                                                   int G, int C, const uint16_t* P, int E, float* Y) {
+  static_assert(TOK == 1 || TOK == 2, "BF16 or FP8 tokens");
+  if ((int)blockIdx.x < nchunk) {
+    colsum_chunk<TOK>(b, wk, 0, blockIdx.x);
+    return;
+  }
+  typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  constexpr int BK = 64, LD = BK + 8, TM = 64 * WM, TN = 64;
+  constexpr int QA = (TOK == 1 ? 2 : 1) * WM;  // 16-byte loads of tokens per thread and step
+  __shared__ alignas(16) uint16_t as[2][TM][LD];
+  __shared__ alignas(16) uint16_t bs[2][TN][LD];
+  const int t = xcd_remap(blockIdx.x - nchunk, gridDim.x - nchunk), nt = E / TN;
+  const int g0 = t / nt * TM, n0 = t % nt * TN;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  constexpr int PR = TOK == 1 ? 8 : 4;  // threads along a token row's step
+  const int ar = tid / PR, ak = (tid % PR) * (BK / PR);
+  const int bn = 4 * ((lane & 7) + 8 * (wv & 1)), bk = 4 * ((lane >> 3) + 8 * (wv >> 1));
+  u32x4 ra[kProjDepth][QA];
+  u32x2 rb[kProjDepth][4];
+  auto fetch = [&](int s, int k0) {  // past the end: the last step again
+    const int k = min(k0, C - BK);
+#pragma unroll
+    for (int i = 0; i < QA; ++i) {
+      const int64_t at = (int64_t)min(g0 + ar + i * (256 / PR), G - 1) * C + k + ak;
+      ra[s][i] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const uint8_t*>(tok) + at * (TOK == 1 ? 2 : 1));
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) rb[s][i] = *reinterpret_cast<const u32x2*>(P + (int64_t)(k + bk + i) * E + n0 + bn);
+  };
+  auto store = [&](int s, int buf) {
+#pragma unroll
+    for (int i = 0; i < QA; ++i) asm volatile("" : "+v"(ra[s][i]));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(rb[s][i]));
+#pragma unroll
+    for (int i = 0; i < QA; ++i) {
+      uint16_t* p = &as[buf][ar + i * (256 / PR)][ak];
+      if (TOK == 1) {
+        *reinterpret_cast<u32x4*>(p) = ra[s][i];
+      } else {
+        uint32_t h[8];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {  // 16 codes: the high halves of their FP32 values
+          const float4 x = e4m3x4_to_f32(ra[s][i][j]);
+          h[2 * j] = __builtin_amdgcn_perm(__float_as_uint(x.y), __float_as_uint(x.x), 0x07060302u);
+          h[2 * j + 1] = __builtin_amdgcn_perm(__float_as_uint(x.w), __float_as_uint(x.z), 0x07060302u);
+        }
+        *reinterpret_cast<u32x4*>(p) = u32x4{h[0], h[1], h[2], h[3]};
+        *reinterpret_cast<u32x4*>(p + 8) = u32x4{h[4], h[5], h[6], h[7]};
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {  // column bn + j: its half of the four rows' words
+      const uint32_t sel = (j & 1) ? 0x07060302u : 0x05040100u;
+      const uint32_t lo = __builtin_amdgcn_perm(rb[s][1][j >> 1], rb[s][0][j >> 1], sel);
+      const uint32_t hi = __builtin_amdgcn_perm(rb[s][3][j >> 1], rb[s][2][j >> 1], sel);
+      *reinterpret_cast<u32x2*>(&bs[buf][bn + j][bk]) = u32x2{lo, hi};
+    }
+  };
+  const int wm = wv >> 1, wn = wv & 1, row = lane & 31, ks = 8 * (lane >> 5);
+  floatx16 acc[WM] = {};
+#pragma unroll
+  for (int s = 0; s < kProjDepth; ++s) fetch(s, s * BK);
+  for (int kb = 0; kb < C; kb += kProjDepth * BK) {
+#pragma unroll
+    for (int s = 0; s < kProjDepth; ++s) {
+      const int k0 = kb + s * BK, buf = s & 1;
+      if (k0 >= C) break;  // uniform
+      store(s, buf);
+      fetch(s, k0 + kProjDepth * BK);
+      __syncthreads();  // one per step: a buffer is written again two steps later
+#pragma unroll
+      for (int kk = 0; kk < BK; kk += 16) {
+        const bf16x8 y = *reinterpret_cast<const bf16x8*>(&bs[buf][32 * wn + row][kk + ks]);
+#pragma unroll
+        for (int i = 0; i < WM; ++i) {
+          const bf16x8 x = *reinterpret_cast<const bf16x8*>(&as[buf][32 * (WM * wm + i) + row][kk + ks]);
+          acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, y, acc[i], 0, 0, 0);
+        }
+      }
     }
   }
-  // acc[v]: row 32 wg + 8 (v >> 2) + 4 (lane >> 5) + (v & 3), column 32 wn + (lane & 31)
-  const int n = n0 + 32 * wn + (lane & 31);
+  // acc[.][v]: row 8 (v >> 2) + 4 (lane >> 5) + (v & 3), column lane & 31
+  const int n = n0 + 32 * wn + row;
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const int g = g0 + 32 * wg + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-    if (g < G) Y[(int64_t)g * E + n] = acc[v];
+  for (int i = 0; i < WM; ++i) {
+    const int gw = g0 + 32 * (WM * wm + i) + 4 * (lane >> 5);
+    float sc[16];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) sc[v] = TOK == 2 ? scale[min(gw + 8 * (v >> 2) + (v & 3), G - 1)] : 1.f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int g = gw + 8 * (v >> 2) + (v & 3);
+      if (g < G) Y[(int64_t)g * E + n] = TOK == 2 ? acc[i][v] * sc[v] : acc[i][v];
+    }
   }
 }
 
@@ -497,27 +716,53 @@ __global__ __launch_bounds__(256) void k_heat_factor(const float* Y, int G, int 
   if (lane == 0) f[r] = a > 0.f ? D[r] / __builtin_sqrtf(a) : 0.f;
 }
 
-void launch_heatmap(const void* tok, int tok_dtype, const float* scale, int G, int C, const void* P, int p_bf16, int E,
-                    const void* text, int text_bf16, int q, const float* D, float* Y, float* fac, float* inv_text,
-                    float* heat, hipStream_t st) {
-  const dim3 pg((G + 63) / 64, E / 64);
-  auto proj = [&](auto tk, auto pb) {
-    constexpr int T = decltype(tk)::value, B = decltype(pb)::value;
-    hipLaunchKernelGGL((k_tokproj<T, B>), pg, dim3(256), 0, st, tok, scale, G, C, P, E, Y);
+// tokens, their statistics and P to Y and r (k_mean and k_resid after the projection)
+static void launch_tokproj(const Batch& b, const Work& w, const void* tok, const float* scale, int G, const void* P,
+                           int p_bf16, int E, float* Y, hipStream_t st) {
+  const int C = b.C, nchunk = b.nchunk, dt = b.tok_dtype;
+  auto go = [&](auto kernel, int tm, int tn, auto p) {
+    hipLaunchKernelGGL(kernel, dim3(nchunk + (G + tm - 1) / tm * (E / tn)), dim3(256), 0, st, b, w, nchunk, tok, scale, G,
+                       C, p, E, Y);
   };
+  if (dt != 0 && p_bf16) {
+    const uint16_t* p = static_cast<const uint16_t*>(P);
+    // taller tiles read P half as often, once there are four 64 x 64 tiles per CU
+    // (whole call, 64 / 128 rows: 68 x 120 tokens x 1280 x 1024 FP8 89 / 80 us,
+    // 45 x 80 x 1024 x 768 47.5 / 48.2, 30 x 40 x 1024 x 768 38.1 / 40.3)
+    const bool tall = (int64_t)((G + 63) / 64) * (E / 64) >= 1024;
+    if (dt == 1) { if (tall) go(k_tokproj16<1, 2>, 128, 64, p); else go(k_tokproj16<1, 1>, 64, 64, p); }
+    else { if (tall) go(k_tokproj16<2, 2>, 128, 64, p); else go(k_tokproj16<2, 1>, 64, 64, p); }
+    return;
+  }
+  auto fp32 = [&](auto tk, auto pb) { go(k_tokproj<decltype(tk)::value, decltype(pb)::value>, 64, 64, P); };
   using Z = std::integral_constant<int, 0>;
   using O = std::integral_constant<int, 1>;
   using T2 = std::integral_constant<int, 2>;
-  if (tok_dtype == 0) { if (p_bf16) proj(Z{}, O{}); else proj(Z{}, Z{}); }
-  else if (tok_dtype == 1) { if (p_bf16) proj(O{}, O{}); else proj(O{}, Z{}); }
-  else { if (p_bf16) proj(T2{}, O{}); else proj(T2{}, Z{}); }
+  if (dt == 1) fp32(O{}, Z{});
+  else if (dt == 2) fp32(T2{}, Z{});
+  else if (p_bf16) fp32(Z{}, O{});
+  else fp32(Z{}, Z{});
+}
+
+void launch_heatmap(const Batch& b, const Work& w, const void* tok, const float* scale, int G, const void* P, int p_bf16,
+                    int E, const void* text, int text_bf16, int q, float eps, float* D, float* Y, float* fac, float* inv_text,
+                    float* heat, hipStream_t st) {
+  launch_tokproj(b, w, tok, scale, G, P, p_bf16, E, Y, st);
+  launch_token_stats(b, w, G, st, true);
+  if (sim_takes_norms(q, G)) {
+    if (text_bf16) launch_sim<1, 2>(Y, G, text, q, E, nullptr, nullptr, w.r, eps, heat, st);
+    else launch_sim<0, 2>(Y, G, text, q, E, nullptr, nullptr, w.r, eps, heat, st);
+    return;
+  }
+  launch_d_from_r(w.r, G, eps, D, st);
   hipLaunchKernelGGL(k_heat_factor, dim3((G + 3) / 4), dim3(256), 0, st, Y, G, E, D, fac);
+  const dim3 ng((q + 3) / 4);
   if (text_bf16) {
-    hipLaunchKernelGGL(k_invnorms<1>, dim3((q + 3) / 4), dim3(256), 0, st, nullptr, 0, text, q, E, nullptr, inv_text);
-    launch_sim<1>(Y, G, text, q, E, fac, inv_text, heat, st);
+    hipLaunchKernelGGL(k_invnorms<1>, ng, dim3(256), 0, st, nullptr, 0, text, q, E, nullptr, inv_text);
+    launch_sim<1, 0>(Y, G, text, q, E, fac, inv_text, nullptr, 0.f, heat, st);
   } else {
-    hipLaunchKernelGGL(k_invnorms<0>, dim3((q + 3) / 4), dim3(256), 0, st, nullptr, 0, text, q, E, nullptr, inv_text);
-    launch_sim<0>(Y, G, text, q, E, fac, inv_text, heat, st);
+    hipLaunchKernelGGL(k_invnorms<0>, ng, dim3(256), 0, st, nullptr, 0, text, q, E, nullptr, inv_text);
+    launch_sim<0, 0>(Y, G, text, q, E, fac, inv_text, nullptr, 0.f, heat, st);
   }
 }
 
@@ -536,11 +781,17 @@ void launch_query(const float* emb, int m, const void* text, int text_bf16, int 
   float* inv_emb = reinterpret_cast<float*>(kb + nb);
   float* inv_text = inv_emb + m;
   const dim3 ng((unsigned)(((int64_t)m + q + 3) / 4));
-  if (text_bf16) hipLaunchKernelGGL(k_invnorms<1>, ng, dim3(256), 0, st, emb, m, text, q, e, inv_emb, inv_text);
-  else hipLaunchKernelGGL(k_invnorms<0>, ng, dim3(256), 0, st, emb, m, text, q, e, inv_emb, inv_text);
-  if (m > 0) {
-    if (text_bf16) launch_sim<1>(emb, m, text, q, e, inv_emb, inv_text, sim, st);
-    else launch_sim<0>(emb, m, text, q, e, inv_emb, inv_text, sim, st);
+  if (m > 0 && sim_takes_norms(q, m)) {
+    if (text_bf16) launch_sim<1, 1>(emb, m, text, q, e, nullptr, nullptr, nullptr, 0.f, sim, st);
+    else launch_sim<0, 1>(emb, m, text, q, e, nullptr, nullptr, nullptr, 0.f, sim, st);
+  } else if (m > 0) {
+    if (text_bf16) {
+      hipLaunchKernelGGL(k_invnorms<1>, ng, dim3(256), 0, st, emb, m, text, q, e, inv_emb, inv_text);
+      launch_sim<1, 0>(emb, m, text, q, e, inv_emb, inv_text, nullptr, 0.f, sim, st);
+    } else {
+      hipLaunchKernelGGL(k_invnorms<0>, ng, dim3(256), 0, st, emb, m, text, q, e, inv_emb, inv_text);
+      launch_sim<0, 0>(emb, m, text, q, e, inv_emb, inv_text, nullptr, 0.f, sim, st);
+    }
   }
   launch_topk(sim, m, q, k, ka, kb, scores, idx, st);
 }
