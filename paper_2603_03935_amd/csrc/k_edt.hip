@@ -677,7 +677,7 @@ __global__ __launch_bounds__(kEdtWaves * 64) __attribute__((amdgpu_waves_per_eu(
 // ---------------------------------------------------------------------------
 __host__ __device__ constexpr int direct_items(int c) { return c == 5 ? 1 : (kEdtWaves >> c); }
 // run lengths past a strip window's ends are needed up to the largest g the
-// tables keep (576, the bound of the tallest class); AREA needs only g > 0
+// tables keep (576, the bound of the tallest class)
 constexpr int kDirRunCap = 576;
 constexpr int kDirRows = 8;   // rows searched together
 constexpr int kDirSteps = 8;  // distances per search step
@@ -1163,7 +1163,7 @@ __device__ __forceinline__ void search_step(const uint2* pu, const uint2* pd, in
   }
 }
 
-// The squared distances (AREA: 1 inside, 0 outside) of the kDirRows rows of
+// The squared distances of the kDirRows rows of
 // one group, whose first table word is `base` (one lane per column) and whose
 // 8-row block is blk, the table's blocks being -1 .. last (mins: block 0's
 // entry of this lane, one every 64 / MC).  Rows are searched together, outward,
@@ -1189,17 +1189,12 @@ __device__ __forceinline__ void search_step(const uint2* pu, const uint2* pd, in
 // the test / now: 16 frames of 1920x1080 with 500 masks, classes 0-4 1629 /
 // 1326 us, tall items 3159 / 2520 us; 64 frames of 640x480 with 60 masks 257 /
 // 235 us; 8 masks of 336x336 24.9 / 23.1 us.
-template <int SPATIAL, int PK, int MC>
+template <int PK, int MC>
 __device__ __forceinline__ void direct_group(const uint2* base, const uint16_t* mins, int blk, int last, int u0, int n,
                                              us2 (&E)[4]) {
   constexpr int C = edt_c(PK);
   const uint2 w0 = base[0], w1 = base[64];
   us2 B[4] = {as_us2(w0.x), as_us2(w0.y), as_us2(w1.x), as_us2(w1.y)};
-  if (SPATIAL != 0) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) E[q] = min2(splat2(C) - B[q], splat2(1));
-    return;
-  }
   if (PK != 2) {
     const bool top = u0 + 3 < n - u0 - 4;  // the nearer padding row is row 0
 #pragma unroll
@@ -1244,7 +1239,7 @@ __device__ __forceinline__ void direct_group(const uint2* base, const uint16_t* 
   for (int q = 0; q < 4; ++q) E[q] = splat2(C) - B[q];
 }
 
-template <int SPATIAL, bool WE, int PK, int MC>
+template <bool WE, int PK, int MC>
 __device__ __forceinline__ void direct_packet(int cls, int s, int S, const uint32_t* recs, const int* words,
                                               uint2* gt_all, uint16_t* m8, float* part, int lane, int kb,
                                               int32_t* e_out) {
@@ -1274,7 +1269,7 @@ __device__ __forceinline__ void direct_packet(int cls, int s, int S, const uint3
       if (b0 + gi >= ub) break;
       const uint2* base = tb + (gi >> 2) * 64;  // row u0 = b0 + gi
       us2 E[kDirRows / 2];
-      direct_group<SPATIAL, PK, MC>(base, m8 + lane / MC, (slot * rows_c + b0 + gi) >> 3,
+      direct_group<PK, MC>(base, m8 + lane / MC, (slot * rows_c + b0 + gi) >> 3,
                                     nblk * (kBlkRows / 8) + kDirBottom / 8 - 1, b0 + gi, n, E);
       int best[kDirRows];
 #pragma unroll
@@ -1282,7 +1277,7 @@ __device__ __forceinline__ void direct_packet(int cls, int s, int S, const uint3
         best[2 * q] = E[q].x;
         best[2 * q + 1] = E[q].y;
       }
-      if (SPATIAL == 0 && PK == 2) {  // rows at least 255 from the outside: exact search
+      if (PK == 2) {  // rows at least 255 from the outside: exact search
         if (max(max(best[0], best[1]), max(best[2], best[3])) >= 65025) search32(base, best);
         if (max(max(best[4], best[5]), max(best[6], best[7])) >= 65025) search32(base + 64, best + 4);
       }
@@ -1297,12 +1292,81 @@ __device__ __forceinline__ void direct_packet(int cls, int s, int S, const uint3
           pr_next += P;
         }
         const int e = best[k];
-        acc += SPATIAL == 0 ? __builtin_amdgcn_sqrtf((float)e) : (float)e;  // e >= 0 integer: no denormals
+        acc += __builtin_amdgcn_sqrtf((float)e);  // e >= 0 integer: no denormals
         if (WE && lane_ok && col >= it.x0 && col <= it.x1)
           e_out[(int64_t)it.gidx * it.fh * it.fw + (int64_t)(y0 - 1 + u) * it.fw + col] = e;
       }
     }
     flush_patch_part(bpart, lane, lane_ok, P, y0, lb, pr, acc);
+  }
+}
+
+// A row's strip window alone (row_window without the runs past it)
+__device__ __forceinline__ uint64_t row_bits(const uint64_t* row, int xs, int x0, int x1) {
+  const int k = xs >> 6, b = xs & 63, ka = x0 >> 6, kz = x1 >> 6;
+  auto word = [&](int q) {
+    uint64_t w = row[min(max(q, ka), kz)];
+    if (q == ka) w &= ~0ull << (x0 & 63);
+    if (q == kz) w &= ~0ull >> (63 - (x1 & 63));
+    return q >= ka && q <= kz ? w : 0ull;
+  };
+  const uint64_t w0 = word(k), w1 = word(k + 1);
+  return b ? (w0 >> b) | (w1 << (64 - b)) : w0;
+}
+
+// AREA: a pixel counts 1, so a packet needs no table and no search, only its
+// mask rows: lane l reads row l & 15 of the (l >> 4)-th of four blocks, then
+// every lane adds up its column's bits, row by row as direct_packet does (whole
+// numbers: the same sums).  Bound by latency: a few dependent reads and the
+// launch (whole call, one 804 x 1189 frame with 34 masks: 110 us with the
+// search's table and no search, 92 so).
+__device__ __forceinline__ void area_packet(int cls, int s, int S, const uint32_t* recs, const int* words, float* part,
+                                            int lane, int kb) {
+  const int rows_c = class_rows(cls), ipp = direct_items(cls);
+  const int nbs = rows_c / kBlkRows, nblk = ipp * nbs, step = S * kEdtWaves;
+  for (int b1 = s + S * kb; b1 < nblk; b1 += 4 * step) {
+    uint64_t win = 0;
+    {
+      const int bl = b1 + step * (lane >> 4);
+      if (bl < nblk) {
+        const int slot = bl / nbs, word = words[slot];
+        const uint32_t* rc = recs + slot * 16;
+        const int n = word >= 0 ? (int)rc[8] : 0, u = (bl - slot * nbs) * kBlkRows + (lane & 15);
+        if (u > 0 && u < n - 1) {
+          const uint64_t* mb = reinterpret_cast<const uint64_t*>(((uint64_t)rc[1] << 32) | rc[0]);
+          const int xs = (int)rc[14] + (word & ((1 << kItemStripBits) - 1)) * strip_width((int)rc[9]);
+          win = row_bits(mb + (int64_t)((int)rc[4] - 1 + u) * (int)rc[11], xs, (int)rc[6], (int)rc[7]);
+        }
+      }
+    }
+    const int lo = (int)(uint32_t)win, hi = (int)(uint32_t)(win >> 32);
+#pragma unroll 1
+    for (int t = 0; t < 4; ++t) {
+      const int b = b1 + step * t;
+      if (b >= nblk) break;
+      const int slot = b / nbs, lb = b - slot * nbs, b0 = lb * kBlkRows;
+      const DirItem it = direct_item(recs, words, slot);
+      const int P = it.P, y0 = it.y0, ua = max(b0, 1), ub = min(b0 + kBlkRows, it.n - 1);
+      if (ua >= ub) continue;
+      const bool lane_ok = lane < it.SW;
+      float* bpart = part + (slot * nbs) * kEdtPartRows * 8;
+      int pr = (y0 - 1 + ua) / P;
+      int pr_next = (pr + 1) * P - (y0 - 1);
+      float acc = 0.f;
+      for (int u = ua; u < ub; ++u) {
+        if (u == pr_next) {
+          flush_patch_part(bpart, lane, lane_ok, P, y0, lb, pr, acc);
+          acc = 0.f;
+          ++pr;
+          pr_next += P;
+        }
+        const int src = 16 * t + u - b0;
+        const uint64_t m = (uint32_t)__builtin_amdgcn_readlane(lo, src) |
+                           ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(hi, src) << 32);
+        acc += (m >> lane) & 1ull ? 1.f : 0.f;
+      }
+      flush_patch_part(bpart, lane, lane_ok, P, y0, lb, pr, acc);
+    }
   }
 }
 
@@ -1314,9 +1378,10 @@ __global__ __launch_bounds__(kEdtWaves * 64) __attribute__((amdgpu_waves_per_eu(
   // Two workgroups of 512 rows share a CU's 160 KB; with 1152 rows the block
   // minima of four columns are kept together so that one fits.
   constexpr int MC = ROWS > 512 ? 4 : 1;
-  constexpr int kTable = (ROWS + kDirTop + kDirBottom) / 4 * 64, kMins = (ROWS + kDirTop + kDirBottom) / 8 * (64 / MC);
-  __shared__ uint2 gt_all[kTable];    // g table, 4 rows per word; zero guard rows at each end
-  __shared__ uint16_t m8_all[kMins];  // largest entry of each 8-row block
+  constexpr int kTable = SPATIAL ? 0 : (ROWS + kDirTop + kDirBottom) / 4 * 64;
+  constexpr int kMins = SPATIAL ? 0 : (ROWS + kDirTop + kDirBottom) / 8 * (64 / MC);
+  __shared__ uint2 gt_all[SPATIAL ? 1 : kTable];    // g table, 4 rows per word; zero guard rows at each end
+  __shared__ uint16_t m8_all[SPATIAL ? 1 : kMins];  // largest entry of each 8-row block
   __shared__ float part_all[ROWS / kBlkRows * kEdtPartRows * 8];
   __shared__ uint32_t recs[kEdtWaves * 16];
   __shared__ int words[kEdtWaves];
@@ -1353,15 +1418,21 @@ __global__ __launch_bounds__(kEdtWaves * 64) __attribute__((amdgpu_waves_per_eu(
     float* part = S == 1 ? part_all : gpart + (int64_t)p * kDirPartFloats;
     uint2* gt = gt_all + kDirTop / 4 * 64;
     uint16_t* m8 = m8_all + kDirTop / 8 * (64 / MC);
+    // the workgroup's next packet (no barrier waits for this atomic before the packet's end)
+    auto take = [&]() {
+      if (queue && threadIdx.x == 0) next = nb + atomicAdd(queue, 1);
+    };
     auto run = [&](auto pk) {
       constexpr int PK = decltype(pk)::value;
       direct_table<PK, MC>(cls, recs, words, gt, m8, lane, kb);
       __syncthreads();
-      // the workgroup's next packet (no barrier waits for this atomic before the packet's end)
-      if (queue && threadIdx.x == 0) next = nb + atomicAdd(queue, 1);
-      direct_packet<SPATIAL, WE, PK, MC>(cls, sh, S, recs, words, gt, m8, part, lane, kb, e_out);
+      take();
+      direct_packet<WE, PK, MC>(cls, sh, S, recs, words, gt, m8, part, lane, kb, e_out);
     };
-    if (ROWS > 512) run(std::integral_constant<int, 2>{});
+    if constexpr (SPATIAL != 0) {
+      take();
+      area_packet(cls, sh, S, recs, words, part, lane, kb);
+    } else if (ROWS > 512) run(std::integral_constant<int, 2>{});
     else if (cls == 4) run(std::integral_constant<int, 1>{});
     else run(std::integral_constant<int, 0>{});
     __syncthreads();

@@ -50,3 +50,8 @@ def test_block_edges(gpu, rows, w):
     band = gpu.patch_weights(b, h, w, 16, distinct=0, edt_layout=1).cpu().numpy()
     direct = gpu.patch_weights(b, h, w, 16, distinct=0, edt_layout=2).cpu().numpy()
     assert np.array_equal(band, direct)
+    # AREA counts pixels: whole numbers, without the column search
+    for P in (14, 16):
+        want = oracle.spatial_weights(bits, w, P, 1)
+        area = gpu.patch_weights(b, h, w, P, spatial=1, distinct=0, edt_layout=2).cpu().numpy()
+        assert np.array_equal(area.reshape(want.shape), want)
