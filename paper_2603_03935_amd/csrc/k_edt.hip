@@ -671,9 +671,10 @@ __global__ __launch_bounds__(kEdtWaves * 64) __attribute__((amdgpu_waves_per_eu(
 // of 512 rows, a class-5 item (up to 1152 rows) is a packet alone.  A
 // workgroup tabulates g for the whole packet, then its 16 wavefronts take the
 // packet's 16-row blocks in a stride.  When the batch has few packets (at
-// most half the resident workgroups), up to kDirSplitMax workgroups share a
-// packet: each tabulates it and searches every S-th block, the block partial
-// sums go to global memory and k_edt_dsums adds them.
+// most half the resident workgroups), two workgroups share a packet, or more
+// (up to kDirSplitMax) while every workgroup has a CU of its own: each
+// tabulates it and searches every S-th block, the block partial sums go to
+// global memory and k_edt_dsums adds them.
 // ---------------------------------------------------------------------------
 __host__ __device__ constexpr int direct_items(int c) { return c == 5 ? 1 : (kEdtWaves >> c); }
 // run lengths past a strip window's ends are needed up to the largest g the
@@ -736,9 +737,14 @@ __device__ __forceinline__ int direct_count(const DirLists& li, bool tall, int* 
   }
   return total;
 }
-// workgroups per packet (uniform over the launch)
+// workgroups per packet (uniform over the launch; grid: two per CU).  Sharing
+// repeats the table build, so beyond two it pays only on idle CUs, where the
+// wavefronts of a packet's deepest blocks then have a SIMD each (8 masks of
+// 336 x 336, two / four / eight workgroups: 23.1 / 19.0 / 17.0 us; 150 packets
+// of 640 x 480, with three on busy CUs: 44 / 47).
 __device__ __forceinline__ int direct_split(bool tall, int total, int grid) {
-  return (!tall && total > 0 && 2 * total <= grid && total <= kDirSplitPackets) ? min(kDirSplitMax, grid / total) : 1;
+  if (tall || total == 0 || 2 * total > grid || total > kDirSplitPackets) return 1;
+  return min(kDirSplitMax, max(2, grid / 2 / total));
 }
 // class of packet p, its first item index and the class's item count
 __device__ __forceinline__ int direct_packet_class(const int* cnt, int p, int& first, int& ccount) {
