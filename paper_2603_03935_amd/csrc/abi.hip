@@ -644,10 +644,14 @@ struct PoolKey {
 std::mutex g_tune_mu;
 std::map<PoolKey, int> g_tune;
 
+constexpr int kPoolFew = 1 << 6;
+
 // launch the pooling GEMM for a choice nt | (unsplit << 4) | ((mw - 1) << 5)
 void launch_pool_choice(const Batch& b, const Work& w, const int4* tiles, hipStream_t st, int choice) {
   const int nt = choice & 15, mw = 1 + ((choice >> 5) & 1);
-  if ((choice >> 4) & 1) {
+  if (choice == kPoolFew) {
+    launch_pool_few(b, w, tiles, st);
+  } else if ((choice >> 4) & 1) {
     Batch b1 = b;
     b1.pool_split = 1;
     launch_pool(b1, w, tiles, st, nt, mw);
@@ -669,7 +673,7 @@ int pool_nt_rule(const Shape& s) {
 // K steps, and fixed K groups are added in group order), so the first call of
 // a shape times each candidate twice and keeps the fastest; captured graphs
 // and untuned calls use a rule.  Returned as nt | (unsplit << 4) | ((mw - 1)
-// << 5).
+// << 5), or kPoolFew (16 x 16 tiles, FP32 operands and tokens).
 int pool_tile_choice(const Plan& p, int tok_dtype, const disc_options& o, bool tune, const Batch& b, const Work& w,
                      const int4* tiles, hipStream_t st, bool* ran) {
   *ran = false;
@@ -684,13 +688,14 @@ int pool_tile_choice(const Plan& p, int tok_dtype, const disc_options& o, bool t
     const auto it = g_tune.find(key);
     if (it != g_tune.end()) return it->second;
   }
-  if (!tune) return pool_nt_rule(s);
+  if (!tune) return pool_few_valid(b) && s.M <= 64 ? kPoolFew : pool_nt_rule(s);
   std::vector<int> cand;
   for (int uns = 0; uns < (s.pool_split > 1 ? 2 : 1); ++uns)
     for (int nt : {1, 2, 4})
       if (pool_nt_valid(s.C, nt)) cand.push_back(nt | (uns << 4));
   for (int nt : {1, 2})  // 128-mask workgroups, K never split
     if (pool_nt_valid(s.C, nt) && s.M > 64) cand.push_back(nt | (1 << 5));
+  if (pool_few_valid(b)) cand.push_back(kPoolFew);
   std::vector<hipEvent_t> ev(4 * cand.size());
   for (auto& e : ev) (void)hipEventCreate(&e);
   for (size_t i = 0; i < cand.size(); ++i)

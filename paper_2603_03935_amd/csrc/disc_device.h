@@ -433,6 +433,9 @@ __host__ __device__ inline int pool_pair_flag(int m0, int m) { return (m0 & 64) 
 // workgroup (1, or 2 with nt <= 2 and K not split)
 void launch_pool(const Batch& b, const Work& w, const int4* tiles, hipStream_t st, int nt = 1, int mw = 1);
 bool pool_nt_valid(int C, int nt);
+// FP32 tokens and operands: 16 x 16 tiles, for few masks
+bool pool_few_valid(const Batch& b);
+void launch_pool_few(const Batch& b, const Work& w, const int4* tiles, hipStream_t st);
 // packed: the k-packed BF16 copy of P is already in the workspace (written
 // by launch_token_stats' pack_proj)
 void launch_proj(const Batch& b, const Work& w, const void* proj, int proj_bf16, hipStream_t st, bool packed = false);

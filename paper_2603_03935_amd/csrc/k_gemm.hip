@@ -453,6 +453,128 @@ __global__ __launch_bounds__(256) void k_pool_reduce(Batch b, Work wk, const int
   pool_store<BF16>(wk, b.frames[t.x], rows, t.z, b.C, lane, wm, wn, total);
 }
 
+// ---------------------------------------------------------------------------
+// FP32 contractions of few rows.  A workgroup computes 16 rows x 16 columns; its
+// four wavefronts take the K groups in turn, each a whole group straight from
+// memory into the operands of v_mfma_f32_16x16x4f32 with all of the group's
+// loads in flight at once, and the group sums are added in group order through
+// LDS.  FP32 MFMA adds products one k after the other, whatever its shape, so
+// the sums have the bits of the tiled kernels.  Those walk a group in 8 to 16
+// steps of load, LDS store, barrier and MFMA chain with one or two steps in
+// flight, on as few as 16 workgroups: what bounded them was the steps' latency,
+// here it is one round of loads and 64 MFMAs of 32 cycles.  Whole calls with 8
+// masks, pooling and projection tiled / so: 336 x 336 71.2 / 58.4 us, 640 x 480
+// 76.4 / 65.9, 1280 x 720 96.1 / 90.3.
+// ---------------------------------------------------------------------------
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+// x[s] of the wavefront's lane row g (16 lanes) becomes x[g] of row s
+__device__ __forceinline__ void rows_to_regs(floatx4& x) {
+  typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+  auto swap32 = [](float& a, float& b) {  // a's upper 32 lanes with b's lower 32
+    const u2 t = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(t.x);
+    b = __uint_as_float(t.y);
+  };
+  auto swap16 = [](float& a, float& b) {  // a's odd rows with b's even rows
+    const u2 t = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(t.x);
+    b = __uint_as_float(t.y);
+  };
+  float v0 = x.x, v1 = x.y, v2 = x.z, v3 = x.w;
+  swap32(v0, v2);
+  swap32(v1, v3);
+  swap16(v0, v1);
+  swap16(v2, v3);
+  x = floatx4{v0, v1, v2, v3};
+}
+
+// Sum over k of [ks, ke) inside the group kb .. kb + 255 (ks and ke multiples
+// of 16).  Lane (n = lane & 15, g = lane >> 4): a_at(k) gives elements k .. k +
+// 3 of its row of A, b_at(k) row k of its column of B; both are called with k
+// clamped to [0, na - 4] and [0, nb - 1], and count as zero past na and nb.
+template <class A, class B>
+__device__ __forceinline__ floatx4 few_group(int kb, int ks, int ke, int na, int nb, A a_at, B b_at) {
+  const int g = (threadIdx.x & 63) >> 4;
+  floatx4 a[16], b[16];
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    const int k = kb + 16 * j;
+    a[j] = a_at(min(k + 4 * g, na - 4));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) b[j][i] = b_at(min(k + 4 * i + g, nb - 1));
+    __builtin_amdgcn_sched_barrier(0);  // in order: a piece waits for its own loads only
+  }
+  floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" : "+v"(a[j]), "+v"(b[j]));
+    const int k = kb + 16 * j;
+    const bool in = k >= ks && k < ke;  // uniform
+    floatx4 x = in && k + 4 * g < na ? a[j] : floatx4{0.f, 0.f, 0.f, 0.f};
+    rows_to_regs(x);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float y = in && k + 4 * i + g < nb ? b[j][i] : 0.f;
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[i], y, acc, 0, 0, 0);
+    }
+  }
+  return acc;
+}
+
+// Adds the groups [ga, gb) in order: thread t ends with element v = t & 3 of
+// lane l = t >> 2 of a tile, row 4 (l >> 4) + v, column l & 15.
+template <int NW, class F>
+__device__ __forceinline__ float few_sum(int ga, int gb, float (*part)[256], F group) {
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  float total = 0.f;
+  for (int g0 = ga; g0 < gb; g0 += NW) {
+    if (g0 + wv < gb) *reinterpret_cast<floatx4*>(&part[wv][4 * lane]) = group(g0 + wv);
+    __syncthreads();
+    for (int w = 0; w < min(NW, gb - g0); ++w) total += part[w][tid & 255];
+    __syncthreads();
+  }
+  return total;
+}
+
+// pooling of FP32 tokens: 16 of these workgroups to a 64 x 64 tile
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void k_pool_few(Batch b, Work wk, const int4* tiles) {
+  const int tix = blockIdx.x >> 4, sub = blockIdx.x & 15;
+  if (tix >= b.dyn[2]) return;
+  const int4 t = tiles[tix];
+  const FrameDesc fd = b.frames[t.x];
+  const int m0 = t.y + 16 * (sub >> 2), n0 = t.z + 16 * (sub & 3), C = b.C, G = fd.G;
+  if (m0 >= fd.m) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  __shared__ int kmin_sh, kmax_sh;
+  __shared__ alignas(16) float part[NW][256];
+  int kbeg, kend;
+  tile_krange(wk, fd, t.y, min(PBM, fd.m - t.y), tid, &kmin_sh, &kmax_sh, kbeg, kend);
+  kbeg = __builtin_amdgcn_readfirstlane(kbeg);
+  kend = __builtin_amdgcn_readfirstlane(kend);
+  const int gbeg = kbeg / kPoolKG, gend = kbeg < kend ? (kend + kPoolKG - 1) / kPoolKG : gbeg;
+  const int ke = (kend + PBK - 1) / PBK * PBK;  // whole steps, as the tiled kernels take them
+  const bool row_ok = m0 + (lane & 15) < fd.m;
+  const float* wrow = reinterpret_cast<const float*>(wk.W) + fd.w_base +
+                      (int64_t)(row_ok ? wk.perm[fd.mask_base + m0 + (lane & 15)] : 0) * fd.Gs;
+  const float* tok = reinterpret_cast<const float*>(fd.tokens) + n0 + (lane & 15);
+  const float total = few_sum<NW>(gbeg, gend, part, [&](int g) {
+    return few_group(
+        g * kPoolKG, kbeg, ke, row_ok ? fd.Gs : 0, G,
+        [&](int k) { return *reinterpret_cast<const floatx4*>(wrow + max(k, 0)); },
+        [&](int k) { return tok[(int64_t)k * C]; });
+  });
+  const int r = 4 * (tid >> 6) + (tid & 3), col = n0 + ((tid >> 2) & 15);
+  if (tid >= 256 || m0 + r >= fd.m) return;
+  const int mi = wk.perm[fd.mask_base + m0 + r], g = fd.mask_base + mi;
+  const float Z = wk.Z[g];
+  const float val = wk.mstat[g] == 0 && Z > 0.f ? total / Z : 0.f;
+  reinterpret_cast<float*>(wk.X)[(int64_t)g * C + col] = val;
+  if (fd.pooled) fd.pooled[(int64_t)mi * C + col] = val;
+}
+
 template <int BF16, int TOK>
 static void launch_pool_t(const Batch& b, const Work& w, const int4* tiles, int nt, int mw, hipStream_t st) {
   const dim3 block(256);
@@ -471,6 +593,17 @@ static void launch_pool_t(const Batch& b, const Work& w, const int4* tiles, int 
   else
     hipLaunchKernelGGL((k_pool<BF16, TOK, 1, 1>), dim3(b.n_tiles * S), block, 0, st, b, w, tiles);
   if (S > 1) hipLaunchKernelGGL((k_pool_reduce<BF16>), dim3(b.n_tiles), block, 0, st, b, w, tiles);
+}
+
+// candidates for up to 128 masks a frame (640 x 480, best tiled / few: 64 masks
+// 90.7 / 83.3 us, 128 94.9 / 89.2, 192 100.7 / 104)
+bool pool_few_valid(const Batch& b) { return b.M <= 128 * b.n_frames && !b.gemm_bf16 && b.tok_dtype == 0; }
+void launch_pool_few(const Batch& b, const Work& w, const int4* tiles, hipStream_t st) {
+  if (b.n_tiles <= 0) return;
+  // with more wavefronts a workgroup's groups take one round; many masks fill the
+  // chip anyway and span few groups each
+  if (b.kgroups > 4 && b.M <= 64) hipLaunchKernelGGL(k_pool_few<8>, dim3(b.n_tiles * 16), dim3(512), 0, st, b, w, tiles);
+  else hipLaunchKernelGGL(k_pool_few<4>, dim3(b.n_tiles * 16), dim3(256), 0, st, b, w, tiles);
 }
 
 // NT must divide C / 64 (the tiles of one mask tile are consecutive in the list)
@@ -601,6 +734,30 @@ __global__ __launch_bounds__(256) void k_proj(Batch b, Work wk, const void* proj
     const int r = 8 * (v >> 2) + 4 * lk + (v & 3);
     if (gbase + r < M) rowp[r][col] = total[v];
   }
+}
+
+// projection of few rows; S = 1: the workgroups write the unnormalised rows
+template <int PBF16>
+__global__ __launch_bounds__(256) void k_proj_few(Batch b, Work wk, const void* proj) {
+  const int C = b.C, E = b.E, M = b.dyn[1];
+  const int gbase = blockIdx.x * 16, c0 = blockIdx.y * 16;
+  if (gbase >= M) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  __shared__ alignas(16) float part[4][256];
+  const float* xrow = reinterpret_cast<const float*>(wk.X) + (int64_t)min(gbase + (lane & 15), M - 1) * C;
+  const int col = c0 + (lane & 15);
+  const float total = few_sum<4>(0, (C + kProjKG - 1) / kProjKG, part, [&](int g) {
+    return few_group(
+        g * kProjKG, 0, C, C, C, [&](int k) { return *reinterpret_cast<const floatx4*>(xrow + k); },
+        [&](int k) {
+          const int64_t at = (int64_t)k * E + col;
+          return PBF16 ? bf2f(reinterpret_cast<const uint16_t*>(proj)[at]) : reinterpret_cast<const float*>(proj)[at];
+        });
+  });
+  const int g = gbase + 4 * (tid >> 6) + (tid & 3);
+  if (g >= M) return;
+  const FrameDesc& fd = b.frames[b.mask_frame[g]];
+  fd.out[(int64_t)(g - fd.mask_base) * E + c0 + ((tid >> 2) & 15)] = total;
 }
 
 // ---------------------------------------------------------------------------
@@ -834,6 +991,10 @@ __global__ __launch_bounds__(256) void k_norm(Batch b, Work wk) {
   if (lane == 0 && fd.status) fd.status[i] = st_in != 0 ? st_in : (ss > 0.f ? 0 : 2);
 }
 
+// rows up to which k_proj_few is used (whole calls of M masks of one 640 x 480
+// frame, tiled / few rows: M = 8 76.4 / 72.3 us, 32 88.9 / 85.7, 64 91.7 / 90.7,
+// 128 95.6 / 94.9, 192 100.6 / 102.0)
+constexpr int kProjFewRows = 64;
 void launch_proj(const Batch& b, const Work& w, const void* proj, int proj_bf16, hipStream_t st, bool packed) {
   if (b.M <= 0) return;
   const dim3 block(256);
@@ -848,6 +1009,15 @@ void launch_proj(const Batch& b, const Work& w, const void* proj, int proj_bf16,
     }
     hipLaunchKernelGGL((k_proj_bf16<64, 64>), dim3((b.M + 63) / 64 * b.proj_split, b.E / 64), block, 0, st, b, w);
   } else {
+    if (b.M <= kProjFewRows) {
+      Batch b1 = b;
+      b1.proj_split = 1;
+      const dim3 grid((b.M + 15) / 16, b.E / 16);
+      if (proj_bf16) hipLaunchKernelGGL((k_proj_few<1>), grid, block, 0, st, b1, w, proj);
+      else hipLaunchKernelGGL((k_proj_few<0>), grid, block, 0, st, b1, w, proj);
+      hipLaunchKernelGGL(k_norm, dim3((b.M + 3) / 4), dim3(256), 0, st, b1, w);
+      return;
+    }
     const dim3 grid((b.M + 31) / 32 * b.proj_split, b.E / 128);
     if (proj_bf16) hipLaunchKernelGGL((k_proj<1>), grid, block, 0, st, b, w, proj);
     else hipLaunchKernelGGL((k_proj<0>), grid, block, 0, st, b, w, proj);
