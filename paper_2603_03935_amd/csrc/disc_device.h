@@ -91,6 +91,29 @@ __device__ __forceinline__ float4 e4m3x4_to_f32(uint32_t w) {
   return make_float4(lo.x, lo.y, hi.x, hi.y);
 }
 
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+// x[s] of the wavefront's lane row g (16 lanes) becomes x[g] of row s
+__device__ __forceinline__ void rows_to_regs(floatx4& x) {
+  typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+  auto swap32 = [](float& a, float& b) {  // a's upper 32 lanes with b's lower 32
+    const u2 t = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(t.x);
+    b = __uint_as_float(t.y);
+  };
+  auto swap16 = [](float& a, float& b) {  // a's odd rows with b's even rows
+    const u2 t = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(t.x);
+    b = __uint_as_float(t.y);
+  };
+  float v0 = x.x, v1 = x.y, v2 = x.z, v3 = x.w;
+  swap32(v0, v2);
+  swap32(v1, v3);
+  swap16(v0, v1);
+  swap16(v2, v3);
+  x = floatx4{v0, v1, v2, v3};
+}
+
 // Workgroup b of a launch runs on XCD b % 8 (each XCD has its own L2).
 // xcd_remap gives each XCD a contiguous range of the n live workgroups of a
 // launch (a bijection of [0, n)), so workgroups that read the same data (the

@@ -466,29 +466,6 @@ __global__ __launch_bounds__(256) void k_pool_reduce(Batch b, Work wk, const int
 // masks, pooling and projection tiled / so: 336 x 336 71.2 / 58.4 us, 640 x 480
 // 76.4 / 65.9, 1280 x 720 96.1 / 90.3.
 // ---------------------------------------------------------------------------
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-
-// x[s] of the wavefront's lane row g (16 lanes) becomes x[g] of row s
-__device__ __forceinline__ void rows_to_regs(floatx4& x) {
-  typedef uint32_t u2 __attribute__((ext_vector_type(2)));
-  auto swap32 = [](float& a, float& b) {  // a's upper 32 lanes with b's lower 32
-    const u2 t = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-    a = __uint_as_float(t.x);
-    b = __uint_as_float(t.y);
-  };
-  auto swap16 = [](float& a, float& b) {  // a's odd rows with b's even rows
-    const u2 t = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-    a = __uint_as_float(t.x);
-    b = __uint_as_float(t.y);
-  };
-  float v0 = x.x, v1 = x.y, v2 = x.z, v3 = x.w;
-  swap32(v0, v2);
-  swap32(v1, v3);
-  swap16(v0, v1);
-  swap16(v2, v3);
-  x = floatx4{v0, v1, v2, v3};
-}
-
 // Sum over k of [ks, ke) inside the group kb .. kb + 255 (ks and ke multiples
 // of 16).  Lane (n = lane & 15, g = lane >> 4): a_at(k) gives elements k .. k +
 // 3 of its row of A, b_at(k) row k of its column of B; both are called with k

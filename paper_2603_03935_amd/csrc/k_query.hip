@@ -16,7 +16,6 @@
 namespace disc {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 template <int BF16>
 __device__ __forceinline__ float4 load_row4(const void* base, int64_t off) {
@@ -342,8 +341,9 @@ static void launch_sim(const float* emb, int m, const void* text, int q, int e, 
                        inv_text, r, eps, sim, (q + ta - 1) / ta);
   };
   if constexpr (SCALE == 0) go(k_sim<BF16, 32, 2, 2, 32, 0>, 64, 64);
-  else if (q <= 16) go(k_sim<BF16, 16, 1, 4, 64, SCALE>, 16, 64);
-  else go(k_sim<BF16, 16, 2, 2, 64, SCALE>, 32, 32);
+  else if constexpr (SCALE == 2) go(k_sim<BF16, 16, 2, 2, 64, 2>, 32, 32);  // (k_heat_few takes up to 16 queries)
+  else if (q <= 16) go(k_sim<BF16, 16, 1, 4, 64, 1>, 16, 64);
+  else go(k_sim<BF16, 16, 2, 2, 64, 1>, 32, 32);
 }
 
 // Order-preserving 64-bit key: larger score first, then smaller index.
@@ -744,11 +744,75 @@ static void launch_tokproj(const Batch& b, const Work& w, const void* tok, const
   else fp32(Z{}, Z{});
 }
 
+// heat[j][i] = D_i cos(text_j, Y_i) for at most 16 queries: 16 patches per
+// workgroup, a quarter of E per wavefront, straight into MFMA operands with all
+// loads in flight, the norms on the way, the quarters added through LDS.  (The
+// similarity tile, 64 patches to a workgroup, has one workgroup per 64 patches
+// and walks E in 8 to 16 steps: 1200 patches x 768 15.5 us, so 8.9; error of
+// the heat-map against 64 bits, rms, 1.9e-8 and 1.2e-8.)
+template <int BF16>
+__global__ __launch_bounds__(256) void k_heat_few(const float* Y, int G, const void* text, int q, int E, const float* r,
+                                                  float eps, float* heat) {
+  constexpr int NC = 16;  // pieces of 16 elements per wavefront: E <= 1024
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, row = lane & 15, g = lane >> 4;
+  const int i0 = xcd_remap(blockIdx.x, gridDim.x) * 16;
+  const int per = E / 4, kb = __builtin_amdgcn_readfirstlane(wv) * per;  // E is a multiple of 128: per, of 32
+  const int64_t bo = (int64_t)min(i0 + row, G - 1) * E + kb + 4 * g, ao = (int64_t)min(row, q - 1) * E + kb + 4 * g;
+  floatx4 a[NC], b[NC];
+#pragma unroll
+  for (int j = 0; j < NC; ++j) {
+    const int k = min(16 * j, per - 16);  // past the quarter: its last piece again
+    const float4 t = load_row4<BF16>(text, ao + k);
+    a[j] = floatx4{t.x, t.y, t.z, t.w};
+    b[j] = *reinterpret_cast<const floatx4*>(Y + bo + k);
+  }
+  __shared__ float red[16];
+  __shared__ alignas(16) float part[4][256];
+  __shared__ float na[4][16], nb[4][16];
+  const float denom = sum_1024(r, G, red) / (float)G + eps;
+  floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+  float sa = 0.f, sb = 0.f;
+#pragma unroll
+  for (int j = 0; j < NC; ++j) {
+    const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+    floatx4 x = 16 * j < per ? a[j] : zero, y = 16 * j < per ? b[j] : zero;
+    sa += sq4(make_float4(x.x, x.y, x.z, x.w));
+    sb += sq4(make_float4(y.x, y.y, y.z, y.w));
+    rows_to_regs(x);
+    rows_to_regs(y);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[s], y[s], acc, 0, 0, 0);
+  }
+  sa += __shfl_xor(sa, 32);
+  sa += __shfl_xor(sa, 16);
+  sb += __shfl_xor(sb, 32);
+  sb += __shfl_xor(sb, 16);
+  *reinterpret_cast<floatx4*>(&part[wv][4 * lane]) = acc;
+  if (g == 0) {
+    na[wv][row] = sa;
+    nb[wv][row] = sb;
+  }
+  __syncthreads();
+  // thread t: element v = t & 3 of lane l = t >> 2: query 4 (l >> 4) + v, patch l & 15
+  const int j = 4 * (tid >> 6) + (tid & 3), n = (tid >> 2) & 15, i = i0 + n;
+  if (j >= q || i >= G) return;
+  const float t = (part[0][tid] + part[1][tid]) + (part[2][tid] + part[3][tid]);
+  const float ta = (na[0][j] + na[1][j]) + (na[2][j] + na[3][j]), tb = (nb[0][n] + nb[1][n]) + (nb[2][n] + nb[3][n]);
+  const float f = tb > 0.f ? r[i] / denom / __builtin_sqrtf(tb) : 0.f;
+  heat[(int64_t)j * G + i] = t * f * inv_norm(ta);
+}
+
 void launch_heatmap(const Batch& b, const Work& w, const void* tok, const float* scale, int G, const void* P, int p_bf16,
                     int E, const void* text, int text_bf16, int q, float eps, float* D, float* Y, float* fac, float* inv_text,
                     float* heat, hipStream_t st) {
   launch_tokproj(b, w, tok, scale, G, P, p_bf16, E, Y, st);
   launch_token_stats(b, w, G, st, true);
+  if (q <= 16) {
+    const dim3 grid((G + 15) / 16);
+    if (text_bf16) hipLaunchKernelGGL(k_heat_few<1>, grid, dim3(256), 0, st, Y, G, text, q, E, w.r, eps, heat);
+    else hipLaunchKernelGGL(k_heat_few<0>, grid, dim3(256), 0, st, Y, G, text, q, E, w.r, eps, heat);
+    return;
+  }
   if (sim_takes_norms(q, G)) {
     if (text_bf16) launch_sim<1, 2>(Y, G, text, q, E, nullptr, nullptr, w.r, eps, heat, st);
     else launch_sim<0, 2>(Y, G, text, q, E, nullptr, nullptr, w.r, eps, heat, st);

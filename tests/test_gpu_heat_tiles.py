@@ -1,7 +1,7 @@
 """disc_query_heatmap at the edges of its tiles: the BF16 contraction with 64
 and 128 token rows (one step of K up to more than its prefetch holds), the FP32
-one, query tiles of 16 and 32 with the norms taken on the way,
-and 64 with separate norms; every pair of token and projection type.
+one, up to 16 queries with E in quarters,
+query tiles of 32 with the norms taken on the way and 64 with separate norms; every pair of token and projection type.
 
 Against the definition in float64 on the stored values.  The arithmetic is
 FP32 over K = C and K = E, each sum's error near sqrt(K) 2^-24 of its terms'
