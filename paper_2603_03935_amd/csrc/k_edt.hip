@@ -670,7 +670,7 @@ __global__ __launch_bounds__(kEdtWaves * 64) __attribute__((amdgpu_waves_per_eu(
 // Packets: class c <= 4 items (2^c x 32 rows) are packed 16 >> c to a packet
 // of 512 rows, a class-5 item (up to 1152 rows) is a packet alone.  A
 // workgroup tabulates g for the whole packet, then its 16 wavefronts take the
-// packet's 16-row blocks in a stride.  When the batch has few packets (at
+// packet's 16-row blocks one after the other.  When the batch has few packets (at
 // most half the resident workgroups), two workgroups share a packet, or more
 // (up to kDirSplitMax) while every workgroup has a CU of its own: each
 // tabulates it and searches every S-th block, the block partial sums go to
@@ -1193,8 +1193,8 @@ __device__ __forceinline__ void search_step(const uint2* pu, const uint2* pd, in
 // VALU-bound (62-74 % busy; the rest is the ends of packets, where few
 // wavefronts are left).  Kernel times, four rows and distances at a time without
 // the test / now: 16 frames of 1920x1080 with 500 masks, classes 0-4 1629 /
-// 1326 us, tall items 3159 / 2520 us; 64 frames of 640x480 with 60 masks 257 /
-// 235 us; 8 masks of 336x336 24.9 / 23.1 us.
+// 1337 us, tall items 3159 / 2385 us; 64 frames of 640x480 with 60 masks 257 /
+// 229 us; 8 masks of 336x336 24.9 / 17.0 us.
 template <int PK, int MC>
 __device__ __forceinline__ void direct_group(const uint2* base, const uint16_t* mins, int blk, int last, int u0, int n,
                                              us2 (&E)[4]) {
@@ -1248,16 +1248,26 @@ __device__ __forceinline__ void direct_group(const uint2* base, const uint16_t* 
 template <bool WE, int PK, int MC>
 __device__ __forceinline__ void direct_packet(int cls, int s, int S, const uint32_t* recs, const int* words,
                                               uint2* gt_all, uint16_t* m8, float* part, int lane, int kb,
-                                              int32_t* e_out) {
+                                              int32_t* e_out, int* todo) {
   own(lane);
   const int rows_c = class_rows(cls), ipp = direct_items(cls);
   const int nbs = rows_c / kBlkRows;  // blocks per slot
   const int nblk = ipp * nbs;         // blocks of the packet
 
   // ---- search: this workgroup's blocks (every S-th from s), one wavefront
-  // per block in a stride, kDirRows rows at a time (direct_group); each
-  // group's rows are then added in row order. ----
-  for (int b = s + S * kb; b < nblk; b += S * kEdtWaves) {
+  // per block, kDirRows rows at a time (direct_group); each group's rows are
+  // then added in row order.  The wavefronts take the next block from a counter
+  // in LDS: a block's cost grows with its depth.  A single item's blocks go from
+  // its middle outwards, the deepest first (tall items, blocks in a stride
+  // before: 16 frames of 1920x1080 2520 -> 2385 us, ragged batch 78 -> 67; 64
+  // frames of 640x480 235 -> 229). ----
+  const int live = ipp == 1 ? (__builtin_amdgcn_readfirstlane(recs[8]) + kBlkRows - 1) / kBlkRows : nblk;
+  for (;;) {
+    int b = 0;
+    if (lane == 0) b = atomicAdd(todo, 1);
+    b = s + S * __builtin_amdgcn_readfirstlane(b);
+    if (b >= live) break;
+    if (ipp == 1) b = (live - 1) / 2 + ((b & 1) ? (b + 1) / 2 : -(b / 2));
     const int slot = b / nbs, lb = b - slot * nbs, b0 = lb * kBlkRows;
     const DirItem it = direct_item(recs, words, slot);
     const int n = it.n, P = it.P, y0 = it.y0;
@@ -1392,7 +1402,7 @@ __global__ __launch_bounds__(kEdtWaves * 64) __attribute__((amdgpu_waves_per_eu(
   __shared__ uint32_t recs[kEdtWaves * 16];
   __shared__ int words[kEdtWaves];
   __shared__ DirLists lists;
-  __shared__ int taken;
+  __shared__ int taken, todo;
   const int lane = threadIdx.x & 63, kb = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   for (int i = threadIdx.x; i < kTable; i += kEdtWaves * 64) gt_all[i] = make_uint2(0u, 0u);
   for (int i = threadIdx.x; i < kMins; i += kEdtWaves * 64) m8_all[i] = 0;
@@ -1430,10 +1440,11 @@ __global__ __launch_bounds__(kEdtWaves * 64) __attribute__((amdgpu_waves_per_eu(
     };
     auto run = [&](auto pk) {
       constexpr int PK = decltype(pk)::value;
+      if (threadIdx.x == 0) todo = 0;
       direct_table<PK, MC>(cls, recs, words, gt, m8, lane, kb);
       __syncthreads();
       take();
-      direct_packet<WE, PK, MC>(cls, sh, S, recs, words, gt, m8, part, lane, kb, e_out);
+      direct_packet<WE, PK, MC>(cls, sh, S, recs, words, gt, m8, part, lane, kb, e_out, &todo);
     };
     if constexpr (SPATIAL != 0) {
       take();
