@@ -127,21 +127,23 @@ __device__ __forceinline__ void pool_rows(const Work& wk, const FrameDesc& fd, i
 
 // divide by Z, store X (GEMM dtype) and the optional FP32 pooled output
 template <int BF16>
+__device__ __forceinline__ void pool_store_one(const Work& wk, const FrameDesc& fd, const int4& rw, int col, int C,
+                                               float sum) {
+  if (rw.x < 0) return;
+  const float val = rw.w ? sum / __int_as_float(rw.z) : 0.f;
+  if (BF16)
+    reinterpret_cast<uint16_t*>(wk.X)[(int64_t)rw.x * C + col] = f2bf(val);
+  else
+    reinterpret_cast<float*>(wk.X)[(int64_t)rw.x * C + col] = val;
+  if (fd.pooled) fd.pooled[(int64_t)rw.y * C + col] = val;
+}
+template <int BF16>
 __device__ __forceinline__ void pool_store(const Work& wk, const FrameDesc& fd, const int4* rows, int n0, int C,
                                            int lane, int wm, int wn, const floatx16& acc) {
   const int col = n0 + 32 * wn + (lane & 31);
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const int r = 32 * wm + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-    const int4 rw = rows[r];
-    if (rw.x < 0) continue;
-    const float val = rw.w ? acc[v] / __int_as_float(rw.z) : 0.f;
-    if (BF16)
-      reinterpret_cast<uint16_t*>(wk.X)[(int64_t)rw.x * C + col] = f2bf(val);
-    else
-      reinterpret_cast<float*>(wk.X)[(int64_t)rw.x * C + col] = val;
-    if (fd.pooled) fd.pooled[(int64_t)rw.y * C + col] = val;
-  }
+  for (int v = 0; v < 16; ++v)
+    pool_store_one<BF16>(wk, fd, rows[32 * wm + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)], col, C, acc[v]);
 }
 
 // grid: (tiles / NT) x S; workgroup (super-tile, s) takes the s-th share of the
@@ -424,33 +426,44 @@ __global__ __launch_bounds__(256) void k_pool(Batch b, Work wk, const int4* tile
   }
 }
 
-// split K: add each tile's stored group sums in group order, then store
+// split K: add each tile's stored group sums in group order, then store.  Four
+// workgroups per tile, one for the part of each of its wavefronts: thread 4 l + i
+// takes elements 4 i .. 4 i + 3 of lane l, so that loads are 4 KB in a row, eight
+// groups in flight.  Bound by latency and the partial sums' bytes (ragged batch,
+// 96 tiles of up to 19 groups: 6.6 us; one workgroup per tile, 64 bytes per
+// thread and group, one group at a time 12.2).
 template <int BF16>
 __global__ __launch_bounds__(256) void k_pool_reduce(Batch b, Work wk, const int4* tiles) {
-  const int tix = blockIdx.x;
+  const int tix = blockIdx.x >> 2, wv = blockIdx.x & 3, wm = wv >> 1, wn = wv & 1;
   if (tix >= b.dyn[2]) return;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, wm = wv >> 1, wn = wv & 1;
+  const int tid = threadIdx.x, lane = tid >> 2, i = tid & 3;
   // the tile's K groups and rows, as the first share of the split pass wrote them
   const int4* info = wk.ptile + (int64_t)tix * (PBM + 1);
   __shared__ int4 rows[PBM];
   if (tid < PBM) rows[tid] = info[1 + tid];
   const int4 kr = info[0];
   const int4 t = tiles[tix];
-  floatx16 total = {};
-  const float* gpart = wk.ppart + ((int64_t)tix * b.kgroups) * (PBM * PBN) + tid * 16;
-  for (int grp = kr.x; grp < kr.y; ++grp) {
-    const float4* src = reinterpret_cast<const float4*>(gpart + (int64_t)grp * (PBM * PBN));
+  const float4* src = reinterpret_cast<const float4*>(wk.ppart + (int64_t)tix * b.kgroups * (PBM * PBN) + wv * 1024) + tid;
+  float4 total = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int grp = kr.x; grp < kr.y; grp += 8) {
+    float4 v[8];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float4 v = src[i];
-      total[4 * i] += v.x;
-      total[4 * i + 1] += v.y;
-      total[4 * i + 2] += v.z;
-      total[4 * i + 3] += v.w;
-    }
+    for (int j = 0; j < 8; ++j) v[j] = src[(int64_t)min(grp + j, kr.y - 1) * (PBM * PBN / 4)];
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (grp + j < kr.y) {
+        total.x += v[j].x;
+        total.y += v[j].y;
+        total.z += v[j].z;
+        total.w += v[j].w;
+      }
   }
   __syncthreads();
-  pool_store<BF16>(wk, b.frames[t.x], rows, t.z, b.C, lane, wm, wn, total);
+  const FrameDesc& fd = b.frames[t.x];
+  const int col = t.z + 32 * wn + (lane & 31), r0 = 32 * wm + 8 * i + 4 * (lane >> 5);
+  const float e[4] = {total.x, total.y, total.z, total.w};
+#pragma unroll
+  for (int k = 0; k < 4; ++k) pool_store_one<BF16>(wk, fd, rows[r0 + k], col, b.C, e[k]);
 }
 
 // ---------------------------------------------------------------------------
@@ -569,7 +582,7 @@ static void launch_pool_t(const Batch& b, const Work& w, const int4* tiles, int 
     hipLaunchKernelGGL((k_pool<BF16, TOK, 2, 1>), dim3(b.n_tiles / 2 * S), block, 0, st, b, w, tiles);
   else
     hipLaunchKernelGGL((k_pool<BF16, TOK, 1, 1>), dim3(b.n_tiles * S), block, 0, st, b, w, tiles);
-  if (S > 1) hipLaunchKernelGGL((k_pool_reduce<BF16>), dim3(b.n_tiles), block, 0, st, b, w, tiles);
+  if (S > 1) hipLaunchKernelGGL((k_pool_reduce<BF16>), dim3(b.n_tiles * 4), block, 0, st, b, w, tiles);
 }
 
 // candidates for up to 128 masks a frame (640 x 480, best tiled / few: 64 masks
