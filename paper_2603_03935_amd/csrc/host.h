@@ -85,6 +85,9 @@ void finish_plan(Plan& p, const PlanAcc& a);
 disc_status describe_one(const disc_tokens* tokens, const disc_masks* masks, const disc_proj* proj, disc_out* out,
                          const disc_options* opts, const char* who, FrameIn& f);
 void stage_host(const Plan& p, char* host, char* dev);
+// the staged region of up to kStageFrames frames, written by a kernel from its arguments
+constexpr int kStageFrames = 8;
+void launch_stage(const FrameDesc* fds, const Shape& s, const Layout& L, char* ws, hipStream_t st);
 Batch make_batch(const Plan& p, char* dev, int tok_dtype, int spatial, int distinct);
 Work work_ptrs(char* base, const Layout& L);
 int resolve_gemm(const disc_options* o, int tok_dtype, int proj_dtype);

@@ -47,27 +47,51 @@ disc_status scratch_of(int dev, char** ptr, int* cus) {
   return DISC_OK;
 }
 
-// The staged region of a one-frame plan: what the other entry points upload
-// from the host (frame descriptor, mask -> frame map, pooling tiles in the
-// order (m0, n0), live counts {frames, masks, tiles, 0}, zeroed class
-// counters).
-__global__ void k_stage_frame(FrameDesc d, int32_t M, int32_t C, int32_t n_tiles, FrameDesc* frames,
-                              int32_t* mask_frame, int4* tiles, int32_t* dyn, int32_t* counts) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
+// The staged region of a plan of a few frames, written from the launch's
+// arguments: frame descriptors, mask -> frame map, pooling tiles in the order
+// (frame, m0, n0), live counts {frames, masks, tiles, 0}, zeroed class counters.
+struct StageArgs {
+  FrameDesc f[kStageFrames];
+  int32_t n, M, C, n_tiles;
+};
+__global__ __launch_bounds__(256) void k_stage_frames(StageArgs a, FrameDesc* frames, int32_t* mask_frame, int4* tiles,
+                                                      int32_t* dyn, int32_t* counts) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x, nct = a.C / 64;
   if (i == 0) {
-    frames[0] = d;
-    dyn[0] = 1;
-    dyn[1] = M;
-    dyn[2] = n_tiles;
+    dyn[0] = a.n;
+    dyn[1] = a.M;
+    dyn[2] = a.n_tiles;
     dyn[3] = 0;
   }
-  if (i < kCounters + 1) counts[i] = 0;  // work-list and queue counters and the frame's scale flag
-  const int nct = C / 64;
-  for (int k = i; k < M; k += stride) mask_frame[k] = 0;
-  for (int t = i; t < n_tiles; t += stride) {
-    const int m0 = (t / nct) * 64;
-    tiles[t] = make_int4(0, m0, (t % nct) * 64, pool_pair_flag(m0, M));
+  if (i < kCounters + a.n) counts[i] = 0;  // work-list and queue counters and the frames' scale flags
+  int base = 0;
+#pragma unroll
+  for (int q = 0; q < kStageFrames; ++q) {
+    if (q >= a.n) break;
+    if (i == q) frames[q] = a.f[q];
+    const int m = a.f[q].m, mb = a.f[q].mask_base, nt = (m + 63) / 64 * nct;
+    for (int k = i; k < m; k += stride) mask_frame[mb + k] = q;
+    for (int t = i; t < nt; t += stride) {
+      const int m0 = (t / nct) * 64;
+      tiles[base + t] = make_int4(q, m0, (t % nct) * 64, pool_pair_flag(m0, m));
+    }
+    base += nt;
   }
+}
+
+void launch_stage(const FrameDesc* fds, const Shape& s, const Layout& L, char* ws, hipStream_t st) {
+  StageArgs a{};
+  for (int q = 0; q < s.n_frames; ++q) a.f[q] = fds[q];
+  a.n = s.n_frames;
+  a.M = (int)s.M;
+  a.C = s.C;
+  a.n_tiles = s.n_tiles;
+  // (the counters and scale flags are fewer than a workgroup's threads)
+  static_assert(kCounters + kStageFrames <= 256, "one workgroup clears the counters");
+  const int grid = std::max(1, std::min(64, (std::max(a.M, a.n_tiles) + 255) / 256));
+  hipLaunchKernelGGL(k_stage_frames, dim3(grid), dim3(256), 0, st, a, reinterpret_cast<FrameDesc*>(ws + L.frames),
+                     reinterpret_cast<int32_t*>(ws + L.mask_frame), reinterpret_cast<int4*>(ws + L.tiles),
+                     reinterpret_cast<int32_t*>(ws + L.dyn), reinterpret_cast<int32_t*>(ws + L.counts));
 }
 
 }  // namespace host
@@ -102,12 +126,7 @@ extern "C" disc_status disc_embed_masks_noalloc(const disc_tokens* tokens, const
   int cus = 0;
   if ((st = scratch_of(dev, &ws, &cus))) return st;
   hipStream_t hs = static_cast<hipStream_t>(stream);
-  const int M = (int)p.shape.M, n_tiles = p.shape.n_tiles;
-  const int grid = std::max(1, std::min(64, (std::max(M, n_tiles) + 255) / 256));
-  hipLaunchKernelGGL(k_stage_frame, dim3(grid), dim3(256), 0, hs, d, M, p.shape.C, n_tiles,
-                     reinterpret_cast<FrameDesc*>(ws + p.L.frames), reinterpret_cast<int32_t*>(ws + p.L.mask_frame),
-                     reinterpret_cast<int4*>(ws + p.L.tiles), reinterpret_cast<int32_t*>(ws + p.L.dyn),
-                     reinterpret_cast<int32_t*>(ws + p.L.counts));
+  launch_stage(&d, p.shape, p.L, ws, hs);
   enqueue_path(p, ws, tokens->dtype, o, proj, cus, hs, /*trace=*/false, /*tune=*/false);
   if ((st = check_launch(who))) return st;
   return ok();
