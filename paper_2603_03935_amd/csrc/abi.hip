@@ -15,6 +15,7 @@
 #include "../../include/disc.h"
 #include "disc_device.h"
 #include "host.h"
+#include "side_ws.h"
 
 using namespace disc;
 
@@ -247,47 +248,6 @@ disc_status acquire(hipStream_t st, const Layout& L, const disc_options* opts, C
   }
   cx.dev_ws = static_cast<char*>(w.dev);
   return DISC_OK;
-}
-
-// Workspace for the faster form of a call that can do without any
-// (disc_backproject, disc_voxel_overlap), one buffer per (device, stream),
-// apart from the workspaces above: those calls are safe from several threads
-// on one stream, so g_side_mu is held from here until the call's kernels are
-// enqueued -- the next call's kernels, and a growing buffer's free, then come
-// after them.  Null when bytes is 0, when the stream is being captured (or
-// cannot say), or when there is no memory for it.
-struct SideWs {
-  void* dev = nullptr;
-  size_t bytes = 0;
-};
-std::mutex g_side_mu;
-std::map<std::pair<int, hipStream_t>, SideWs> g_side;
-
-char* side_ws(hipStream_t st, size_t bytes) {
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  int dev = 0;
-  if (bytes == 0) return nullptr;
-  if (hipStreamIsCapturing(st, &cs) != hipSuccess || hipGetDevice(&dev) != hipSuccess) {
-    (void)hipGetLastError();
-    return nullptr;
-  }
-  if (cs != hipStreamCaptureStatusNone) return nullptr;
-  SideWs& w = g_side[{dev, st}];
-  if (w.bytes < bytes) {
-    if (w.dev) {
-      (void)hipStreamSynchronize(st);
-      (void)hipFree(w.dev);
-    }
-    w = SideWs();
-    const size_t want = (size_t)round_up((int64_t)(bytes * 5 / 4), 1 << 16);
-    if (hipMalloc(&w.dev, want) != hipSuccess) {
-      (void)hipGetLastError();
-      w = SideWs();
-      return nullptr;
-    }
-    w.bytes = want;
-  }
-  return static_cast<char*>(w.dev);
 }
 
 // Writes the plan's staged region.  Up to kStageFrames frames go as the
@@ -863,6 +823,7 @@ disc_status disc_embed_masks(const disc_tokens* tokens, const disc_masks* masks,
 
 disc_status disc_release_workspace(void) {
   (void)hipDeviceSynchronize();
+  release_side_ws();
   std::lock_guard<std::mutex> lk(g_ws_mu);
   for (auto& kv : g_ws) {
     if (kv.second.dev) (void)hipFree(kv.second.dev);
@@ -870,10 +831,6 @@ disc_status disc_release_workspace(void) {
     if (kv.second.ev) (void)hipEventDestroy(kv.second.ev);
   }
   g_ws.clear();
-  std::lock_guard<std::mutex> side(g_side_mu);
-  for (auto& kv : g_side)
-    if (kv.second.dev) (void)hipFree(kv.second.dev);
-  g_side.clear();
   return ok();
 }
 
@@ -1215,9 +1172,8 @@ disc_status disc_backproject(const float* depth, const disc_masks* masks, const 
   if (!offsets || !points) return fail(DISC_ERR_INVALID_ARGUMENT, "%s: NULL pointer", who);
   float cf[18];
   cam_floats(cam, cf);
-  std::lock_guard<std::mutex> lk(g_side_mu);
-  char* ws = side_ws(static_cast<hipStream_t>(stream), bp_write_ws_bytes(masks->h, masks->w));
-  launch_bp_write(depth, masks->bits, masks->m, masks->h, masks->w, stride, cf, offsets, points, ws,
+  const SideLease ws(static_cast<hipStream_t>(stream), bp_write_ws_bytes(masks->h, masks->w));
+  launch_bp_write(depth, masks->bits, masks->m, masks->h, masks->w, stride, cf, offsets, points, ws.ptr,
                   static_cast<hipStream_t>(stream));
   if ((st = check_launch(who))) return st;
   return ok();
@@ -1274,9 +1230,8 @@ disc_status disc_voxel_overlap(const int32_t* va, const int32_t* oa, int32_t na,
   if (na < 0 || nb < 0 || np < 0) return fail(DISC_ERR_INVALID_ARGUMENT, "%s: negative count", who);
   if (np == 0) return ok();
   if (!oa || !ob || !pairs || !counts) return fail(DISC_ERR_INVALID_ARGUMENT, "%s: NULL pointer", who);
-  std::lock_guard<std::mutex> lk(g_side_mu);
-  char* ws = side_ws(static_cast<hipStream_t>(stream), overlap_ws_bytes(na, nb, np));
-  launch_overlap(va, oa, na, vb, ob, nb, pairs, np, counts, ws, static_cast<hipStream_t>(stream));
+  const SideLease ws(static_cast<hipStream_t>(stream), overlap_ws_bytes(na, nb, np));
+  launch_overlap(va, oa, na, vb, ob, nb, pairs, np, counts, ws.ptr, static_cast<hipStream_t>(stream));
   disc_status st;
   if ((st = check_launch(who))) return st;
   return ok();
