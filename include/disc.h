@@ -331,7 +331,11 @@ disc_status disc_backproject_count(const float* depth, const disc_masks* masks, 
                                    int32_t stride, int32_t* offsets, void* stream);
 /* Back-projection, pass 2: the world points of each mask, in row-major pixel
  * order, written to points [offsets[i] ...][3] FP32 (the caller reads
- * offsets[m] after pass 1 to size points).  Same arguments as pass 1. */
+ * offsets[m] after pass 1 to size points).  Same arguments as pass 1.
+ * This call and disc_voxel_overlap keep a work buffer per (device, stream) of
+ * their own (at most 512 MB) until disc_release_workspace.  On a stream that
+ * is being captured and on hipStreamPerThread (one handle for every thread's
+ * stream) they do without: the same results from slower kernels. */
 disc_status disc_backproject(const float* depth, const disc_masks* masks, const disc_camera* cam, int32_t stride,
                              const int32_t* offsets, float* points, void* stream);
 

@@ -15,14 +15,19 @@ namespace disc {
 namespace host {
 
 constexpr size_t kSideMax = (size_t)128 << 20;  // a call that asks for more does without
+constexpr int kSideOld = 16;                    // outgrown buffers: doublings from 64 KB to beyond kSideMax
 
 struct SideWs {
+  std::mutex mu;  // held while a call takes the buffer and enqueues its kernels
   void* dev = nullptr;
   size_t bytes = 0;
   hipEvent_t used = nullptr;  // after the last call's kernels (not on the null stream)
   bool recorded = false;
+  void* old[kSideOld];  // outgrown buffers: kernels in flight may still use them
+  int n_old = 0;
 };
-inline std::mutex g_side_mu;  // held while a call takes a buffer and enqueues its kernels
+// Entries are never erased, so a reference to one stays valid.
+inline std::mutex g_side_mu;
 inline std::map<std::pair<int, hipStream_t>, SideWs> g_side;
 
 // The buffer of a call that enqueues its kernels while the lease lives; ptr is
@@ -34,7 +39,11 @@ inline std::map<std::pair<int, hipStream_t>, SideWs> g_side;
 // can come back for another stream while the destroyed one's kernels still run,
 // so each call waits, on the device, for the event that the one before recorded
 // (about 2 us a call).  The null stream's handle is never another's, so there
-// stream order is enough.
+// stream order is enough.  Nothing here waits on the host or frees memory, and
+// only calls on one stream share a mutex beyond the table's look-up: a buffer
+// that grows at least doubles, and the outgrown ones (together smaller than it)
+// are kept until release_side_ws.  Memory is allocated in the relaxed capture
+// mode, so that a graph which another thread captures meanwhile is not broken.
 class SideLease {
  public:
   SideLease(hipStream_t st, size_t bytes) : st_(st) {
@@ -46,11 +55,14 @@ class SideLease {
       return;
     }
     if (cs != hipStreamCaptureStatusNone) return;
-    g_side_mu.lock();
-    ws_ = &g_side[{dev, st}];
+    {
+      std::lock_guard<std::mutex> lk(g_side_mu);
+      ws_ = &g_side[{dev, st}];
+    }
+    ws_->mu.lock();
     if (!take(bytes)) {
       (void)hipGetLastError();
-      g_side_mu.unlock();
+      ws_->mu.unlock();
       ws_ = nullptr;
       return;
     }
@@ -65,7 +77,7 @@ class SideLease {
         (void)hipStreamSynchronize(st_);
       }
     }
-    g_side_mu.unlock();
+    ws_->mu.unlock();
   }
   SideLease(const SideLease&) = delete;
   SideLease& operator=(const SideLease&) = delete;
@@ -82,15 +94,15 @@ class SideLease {
     }
     if (ws_->recorded && hipStreamWaitEvent(st_, ws_->used, 0) != hipSuccess) return false;
     if (ws_->bytes >= bytes) return true;
-    if (ws_->dev) {
-      (void)hipStreamSynchronize(st_);
-      (void)hipFree(ws_->dev);
-      ws_->dev = nullptr;
-      ws_->bytes = 0;
-    }
-    const size_t want = (bytes + bytes / 4 + 0xFFFF) & ~(size_t)0xFFFF;
+    if (ws_->n_old == kSideOld) return false;
+    const size_t want = (std::max(bytes + bytes / 4, 2 * ws_->bytes) + 0xFFFF) & ~(size_t)0xFFFF;
     void* p = nullptr;
-    if (hipMalloc(&p, want) != hipSuccess) return false;
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    const hipError_t e = hipMalloc(&p, want);
+    if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (e != hipSuccess) return false;
+    if (ws_->dev) ws_->old[ws_->n_old++] = ws_->dev;
     ws_->dev = p;
     ws_->bytes = want;
     return true;
@@ -107,12 +119,15 @@ inline void release_side_ws() {
   (void)hipGetDevice(&dev);
   for (auto& kv : g_side) {
     SideWs& w = kv.second;
+    std::lock_guard<std::mutex> one(w.mu);
     if (!w.dev) continue;
     (void)hipSetDevice(kv.first.first);
     (void)hipDeviceSynchronize();
     if (w.used) (void)hipEventDestroy(w.used);
     w.used = nullptr;
     w.recorded = false;
+    for (int i = 0; i < w.n_old; ++i) (void)hipFree(w.old[i]);
+    w.n_old = 0;
     (void)hipFree(w.dev);
     w.dev = nullptr;
     w.bytes = 0;

@@ -1,7 +1,8 @@
 """disc_backproject and disc_voxel_overlap beside other streams, threads and
 graph captures: threads that each work on their own stream under one handle,
-a buffer that grows and is then used by a smaller call, and the forms that a
-capture takes against the ones that use the workspace.  Every result exactly as by a call alone."""
+a buffer that grows and is then used by a smaller call, a capture in another
+thread, and the forms that a capture takes against the ones that use the
+workspace.  Every result exactly as by a call alone."""
 import ctypes
 import threading
 
@@ -126,3 +127,38 @@ def test_captured_forms(gpu):
         t.cuda.synchronize()
         assert f.same()
 
+
+def test_capture_in_another_thread(gpu):
+    """A graph captured (globally) while another thread's call makes its buffer and grows it."""
+    t = torch()
+    frames = [Frame(gpu, 51, 97, 130), Frame(gpu, 52, 720, 1280)]
+    st, x, y = t.cuda.Stream(), t.arange(1000, device="cuda"), t.zeros(1000, dtype=t.int64, device="cuda")
+    for f in frames:
+        f.clear()
+    t.cuda.synchronize()
+    inside, done, errors = threading.Event(), threading.Event(), []
+
+    def work():
+        try:
+            inside.wait()
+            for f in frames:
+                f.write(st.cuda_stream)
+                f.overlap(st.cuda_stream)
+        except AssertionError as e:
+            errors.append(e)
+        done.set()
+
+    th = threading.Thread(target=work)
+    th.start()
+    g = t.cuda.CUDAGraph()
+    with t.cuda.graph(g):
+        y.add_(x)
+        inside.set()
+        done.wait()
+        y.add_(x)
+    th.join()
+    for _ in range(3):
+        g.replay()
+    t.cuda.synchronize()
+    assert not errors and all(f.same() for f in frames)
+    assert t.equal(y, 6 * x)

@@ -1,6 +1,8 @@
 """The workspace of disc_backproject and disc_voxel_overlap (csrc/side_ws.h)
 against a HIP runtime that only writes down its calls (CPU only): which
-streams get a buffer, and that uses of one are ordered on the device."""
+streams get a buffer, that uses of one are ordered on the device, and that
+nothing waits, frees or allocates in a way that another stream or another
+thread's graph capture would notice."""
 import os
 import subprocess
 
@@ -90,6 +92,20 @@ int main(int argc, char** argv) {
   } else if (t == "null_stream") {  // the one stream of its handle, never destroyed: its own order is enough
     void* p = use(nullptr, 1000);
     CHECK(p && use(nullptr, 500) == p && count("wait") == 0 && count("record") == 0 && count("sync") == 0);
+  } else if (t == "growth") {  // a larger buffer while kernels use the smaller one
+    void* p = use(A, 1000);
+    const size_t first = last_bytes;
+    void* q = use(A, first + 1);
+    CHECK(p && q && p != q && last_bytes >= 2 * first);
+    CHECK(use(A, 10) == q);
+    CHECK(count("free") == 0 && count("sync") == 0);
+    CHECK(count("wait 10") == 2 && count("record 10") == 3);
+    release_side_ws();
+    CHECK(count("free") == 2 && count("sync") == 1);
+    CHECK(calls[calls.size() - 3] == "sync all");
+    CHECK(use(A, 1000) != nullptr);
+  } else if (t == "capture_elsewhere") {
+    CHECK(use(A, 1000) && count("relaxed malloc") == 1 && mode == hipStreamCaptureModeGlobal);
   } else if (t == "no_buffer") {
     CHECK(!use(A, 0) && !use(A, ((size_t)128 << 20) + 1));
     capturing = true;
@@ -102,6 +118,20 @@ int main(int argc, char** argv) {
   } else if (t == "no_mark") {  // the end of a use cannot be marked: the next must not overtake it
     no_record = true;
     CHECK(use(A, 1000) && count("sync 10") == 1);
+  } else if (t == "other_streams") {  // one stream's buffer grows while another's call goes on
+    CHECK(use(B, 1000));
+    malloc_waits = true;
+    in_malloc = false;
+    std::thread g([&] { use(A, 1000); });
+    while (!in_malloc) std::this_thread::yield();
+    std::atomic<bool> done{false};
+    std::thread b([&] { use(B, 1000); done = true; });
+    for (int i = 0; i < 2000 && !done; ++i) std::this_thread::sleep_for(std::chrono::milliseconds(1));
+    const bool went = done;
+    malloc_waits = false;
+    g.join();
+    b.join();
+    CHECK(went);
   } else {
     return 2;
   }
@@ -121,7 +151,8 @@ def program(tmp_path_factory):
     return str(d / "t")
 
 
-@pytest.mark.parametrize("what", ["per_thread", "reused_handle", "null_stream", "no_buffer", "no_mark"])
+@pytest.mark.parametrize("what", ["per_thread", "reused_handle", "null_stream", "growth", "capture_elsewhere", "no_buffer", "no_mark",
+                                  "other_streams"])
 def test_side_workspace(program, what):
     r = subprocess.run([program, what], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout
