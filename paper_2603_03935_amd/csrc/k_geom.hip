@@ -182,7 +182,8 @@ __global__ __launch_bounds__(1024) void k_bp_count(const uint64_t* bits, const u
   }
 }
 
-// One workgroup per (mask, block of kBpRows rows): it counts the points of
+// One workgroup per (mask, block of kBpRows rows), the grid's x and y (a
+// dimension holds fewer than 2^32 threads): it counts the points of
 // the mask's earlier rows (popcounts of words that are in L2 by then) to know
 // where its own begin, so that a frame's few large masks spread over the chip;
 // blocks without points leave at once.  36 masks of a 480x640 frame: 104 us
@@ -190,9 +191,8 @@ __global__ __launch_bounds__(1024) void k_bp_count(const uint64_t* bits, const u
 constexpr int kBpRows = 32;
 
 __global__ __launch_bounds__(1024) void k_bp_write_rows(const float* depth, const uint64_t* bits, const uint64_t* valid,
-                                                       int h, int w, int nblk, Cam c, const int32_t* offsets,
-                                                       float* points) {
-  const int i = blockIdx.x / nblk, y0 = (blockIdx.x % nblk) * kBpRows;
+                                                       int h, int w, Cam c, const int32_t* offsets, float* points) {
+  const int i = blockIdx.x, y0 = blockIdx.y * kBpRows;
   const int wq = (w + 63) / 64, w0 = y0 * wq, w1 = min(h, y0 + kBpRows) * wq;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const uint64_t* mb = bits + (int64_t)i * h * wq;
@@ -1062,8 +1062,7 @@ void launch_bp_write(const float* depth, const uint64_t* bits, int m, int h, int
   }
   uint64_t* valid = reinterpret_cast<uint64_t*>(ws);
   launch_bp_valid(depth, h, w, s, to_cam(cam), valid, st);
-  const int nblk = (h + kBpRows - 1) / kBpRows;
-  hipLaunchKernelGGL(k_bp_write_rows, dim3((unsigned)m * (unsigned)nblk), dim3(1024), 0, st, depth, bits, valid, h, w, nblk,
+  hipLaunchKernelGGL(k_bp_write_rows, dim3(m, (h + kBpRows - 1) / kBpRows), dim3(1024), 0, st, depth, bits, valid, h, w,
                      to_cam(cam), offsets, points);
 }
 

@@ -1,0 +1,41 @@
+"""Calls whose work items, at one workgroup each, come to 2^32 threads and more,
+which one dimension of a launch cannot hold: they run, and give what smaller
+calls give."""
+import numpy as np
+import pytest
+
+import disc_inputs as di
+from disc_inputs.scene import depth_scene
+from gpu_common import torch
+from oracle import geometry as og
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def gpu():
+    t = torch()
+    if not t.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2603_03935_amd as disc
+
+    disc.load()
+    return disc
+
+
+def test_backproject_masks(gpu):
+    """2^21 masks of two row blocks; a few of them, the last among them, have points."""
+    t = torch()
+    h, w, m = 33, 64, (1 << 21) + 3
+    rng = np.random.default_rng(3)
+    depth = rng.uniform(0.5, 4.0, (h, w)).astype(np.float32)
+    cam = depth_scene(1, 32, 64, n_obj=2, min_area=1).camera
+    some = di.pack_masks((rng.random((5, h, w)) < 0.4).astype(np.uint8))
+    at = np.array([0, 1, 70001, m - 2, m - 1])
+    bits = t.zeros((m, h, 1), dtype=t.int64, device="cuda")
+    bits[t.from_numpy(at).cuda()] = t.from_numpy(some.view(np.int64)).cuda()
+    pts, off = gpu.backproject(t.from_numpy(depth).cuda(), bits, h, w, cam, 1)
+    want, woff = og.backproject(depth, some, w, cam, 1)
+    off = off.cpu().numpy()
+    assert np.array_equal(off[at], woff[:-1]) and np.array_equal(off[at + 1], woff[1:])
+    assert np.array_equal(pts.cpu().numpy().view(np.uint32), want.view(np.uint32))
