@@ -81,6 +81,7 @@ def test_threads_with_their_own_default_stream(gpu):
                 for _ in range(20):
                     f.write(PER_THREAD)
                     f.overlap(PER_THREAD)
+                torch().cuda.synchronize()  # a thread's stream ends with it, perhaps before its work
             except AssertionError as e:
                 errors.append(e)
 
