@@ -1162,12 +1162,14 @@ void launch_overlap(const int32_t* va, const int32_t* oa, int na, const int32_t*
                     const int32_t* pairs, int np, int32_t* out, char* ws, hipStream_t st) {
   if (np <= 0) return;
   VoxBox* boxes = reinterpret_cast<VoxBox*>(ws);
-  if (!boxes) {
-    hipLaunchKernelGGL(k_overlap<0>, dim3(np), dim3(512), 0, st, va, oa, vb, ob, pairs, na, nb, nullptr, out);
-    return;
+  if (boxes) hipLaunchKernelGGL(k_vox_boxes, dim3(na + nb), dim3(1024), 0, st, va, oa, na, vb, ob, boxes);
+  constexpr int kPairs = 1 << 22;  // a launch's dimension holds fewer than 2^32 threads
+  for (int64_t p0 = 0; p0 < np; p0 += kPairs) {
+    const dim3 grid((unsigned)std::min<int64_t>(kPairs, np - p0));
+    const int32_t* pp = pairs + 2 * p0;
+    if (boxes) hipLaunchKernelGGL(k_overlap<1>, grid, dim3(512), 0, st, va, oa, vb, ob, pp, na, nb, boxes, out + p0);
+    else hipLaunchKernelGGL(k_overlap<0>, grid, dim3(512), 0, st, va, oa, vb, ob, pp, na, nb, nullptr, out + p0);
   }
-  hipLaunchKernelGGL(k_vox_boxes, dim3(na + nb), dim3(1024), 0, st, va, oa, na, vb, ob, boxes);
-  hipLaunchKernelGGL(k_overlap<1>, dim3(np), dim3(512), 0, st, va, oa, vb, ob, pairs, na, nb, boxes, out);
 }
 
 }  // namespace disc

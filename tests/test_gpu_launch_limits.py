@@ -39,3 +39,21 @@ def test_backproject_masks(gpu):
     off = off.cpu().numpy()
     assert np.array_equal(off[at], woff[:-1]) and np.array_equal(off[at + 1], woff[1:])
     assert np.array_equal(pts.cpu().numpy().view(np.uint32), want.view(np.uint32))
+
+
+def test_overlap_pairs(gpu):
+    t = torch()
+    rng = np.random.default_rng(4)
+    sizes = [0, 1, 40, 300, 77]
+    lists = []
+    for c in sizes:
+        code = rng.choice(8 ** 3, size=c, replace=False)
+        cell = np.stack([code // 64, code // 8 % 8, code % 8], -1)
+        lists.append(cell[np.lexsort(cell.T[::-1])])
+    sets = [set(map(tuple, x.tolist())) for x in lists]
+    table = t.tensor([[len(a & b) for b in sets] for a in sets], dtype=t.int32, device="cuda")
+    vox = t.from_numpy(np.concatenate(lists).astype(np.int32)).cuda()
+    off = t.from_numpy(np.cumsum([0] + sizes).astype(np.int32)).cuda()
+    pairs = t.randint(0, 5, ((1 << 23) + 7, 2), device="cuda", dtype=t.int32, generator=t.Generator("cuda").manual_seed(1))
+    got = gpu.voxel_overlap(vox, off, vox, off, pairs)
+    assert t.equal(got, table[pairs[:, 0].long(), pairs[:, 1].long()])
