@@ -337,8 +337,14 @@ template <int BF16, int SCALE>
 static void launch_sim(const float* emb, int m, const void* text, int q, int e, const float* inv_emb,
                        const float* inv_text, const float* r, float eps, float* sim, hipStream_t st) {
   auto go = [&](auto kernel, int ta, int tb) {
-    hipLaunchKernelGGL(kernel, dim3((unsigned)sim_tiles(q, m, ta, tb)), dim3(256), 0, st, emb, m, text, q, e, inv_emb,
-                       inv_text, r, eps, sim, (q + ta - 1) / ta);
+    // queries of a launch: a grid dimension holds fewer than 2^32 threads
+    const int64_t per = std::max<int64_t>(1, (1 << 23) / ((m + tb - 1) / tb)) * ta;
+    for (int64_t j = 0; j < q; j += per) {
+      const int n = (int)std::min<int64_t>(per, q - j);
+      hipLaunchKernelGGL(kernel, dim3((unsigned)sim_tiles(n, m, ta, tb)), dim3(256), 0, st, emb, m,
+                         static_cast<const char*>(text) + j * e * (BF16 ? 2 : 4), n, e, inv_emb,
+                         inv_text ? inv_text + j : nullptr, r, eps, sim + j * m, (n + ta - 1) / ta);
+    }
   };
   if constexpr (SCALE == 0) go(k_sim<BF16, 32, 2, 2, 32, 0>, 64, 64);
   else if constexpr (SCALE == 2) go(k_sim<BF16, 16, 2, 2, 64, 2>, 32, 32);  // (k_heat_few takes up to 16 queries)
@@ -518,8 +524,8 @@ static void topk_scratch(int m, int q, int k, int64_t* a, int64_t* b) {
   if (nch2 > 1) *b = (int64_t)q * nch2 * k;
 }
 
-static void launch_topk(const float* sim, int m, int q, int k, uint64_t* ka, uint64_t* kb, float* scores, int32_t* idx,
-                        hipStream_t st) {
+static void launch_topk_rows(const float* sim, int m, int q, int k, uint64_t* ka, uint64_t* kb, float* scores,
+                             int32_t* idx, hipStream_t st) {
   const int nch = topk_chunks(m, kTopkRow);
   const dim3 blk(kTopkThreads);
   if (nch == 1) {
@@ -538,6 +544,15 @@ static void launch_topk(const float* sim, int m, int q, int k, uint64_t* ka, uin
     n = c * k;
   }
   hipLaunchKernelGGL((k_topk<8, 1, 1>), dim3(q), blk, 0, st, nullptr, ka, n, k, 1, nullptr, scores, idx);
+}
+
+// (rows one after the other in slices: a grid dimension holds fewer than 2^32
+// threads; slices use the same scratch in turn)
+static void launch_topk(const float* sim, int m, int q, int k, uint64_t* ka, uint64_t* kb, float* scores, int32_t* idx,
+                        hipStream_t st) {
+  const int per = (1 << 21) / topk_chunks(m, kTopkRow);
+  for (int64_t j = 0; j < q; j += per)
+    launch_topk_rows(sim + j * m, m, (int)std::min<int64_t>(per, q - j), k, ka, kb, scores + j * k, idx + j * k, st);
 }
 
 // ---------------------------------------------------------------------------

@@ -57,3 +57,20 @@ def test_overlap_pairs(gpu):
     pairs = t.randint(0, 5, ((1 << 23) + 7, 2), device="cuda", dtype=t.int32, generator=t.Generator("cuda").manual_seed(1))
     got = gpu.voxel_overlap(vox, off, vox, off, pairs)
     assert t.equal(got, table[pairs[:, 0].long(), pairs[:, 1].long()])
+
+
+def test_query_rows(gpu):
+    """More query rows than one launch ranks."""
+    t = torch()
+    q, m, k = (1 << 22) + 3, 5, 2
+    g = t.Generator("cuda").manual_seed(2)
+    emb = t.randn(m, 16, device="cuda", generator=g)
+    text = t.randn(q, 16, device="cuda", generator=g).bfloat16()
+    scores, idx, sim = gpu.query_topk(emb, text, k)
+    best, at = sim.sort(dim=1, descending=True, stable=True)
+    assert t.equal(idx, at[:, :k].int()) and t.equal(scores, best[:, :k])
+    for a in range(0, q, 1 << 20):
+        x, y = text[a:a + (1 << 20)].double(), emb.double()
+        want = (x @ y.T) / x.norm(dim=1)[:, None] / y.norm(dim=1)
+        # 16 products and two norms in FP32: below 20 roundings of 2^-24
+        assert (sim[a:a + (1 << 20)] - want).abs().max().item() < 1.2e-6
