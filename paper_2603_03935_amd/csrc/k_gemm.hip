@@ -586,8 +586,11 @@ static void launch_pool_t(const Batch& b, const Work& w, const int4* tiles, int 
 }
 
 // candidates for up to 128 masks a frame (640 x 480, best tiled / few: 64 masks
-// 90.7 / 83.3 us, 128 94.9 / 89.2, 192 100.7 / 104)
-bool pool_few_valid(const Batch& b) { return b.M <= 128 * b.n_frames && !b.gemm_bf16 && b.tok_dtype == 0; }
+// 90.7 / 83.3 us, 128 94.9 / 89.2, 192 100.7 / 104) and launches of fewer than
+// 2^32 threads (16 x 256 to a tile)
+bool pool_few_valid(const Batch& b) {
+  return b.M <= (int64_t)128 * b.n_frames && b.n_tiles < 1 << 20 && !b.gemm_bf16 && b.tok_dtype == 0;
+}
 void launch_pool_few(const Batch& b, const Work& w, const int4* tiles, hipStream_t st) {
   if (b.n_tiles <= 0) return;
   // with more wavefronts a workgroup's groups take one round; many masks fill the

@@ -74,3 +74,18 @@ def test_query_rows(gpu):
         want = (x @ y.T) / x.norm(dim=1)[:, None] / y.norm(dim=1)
         # 16 products and two norms in FP32: below 20 roundings of 2^-24
         assert (sim[a:a + (1 << 20)] - want).abs().max().item() < 1.2e-6
+
+
+def test_pooling_tiles(gpu):
+    """2^15 FP32 frames of one mask, 2048 channels: 2^20 pooling tiles."""
+    t = torch()
+    n, C, E = 1 << 15, 2048, 128
+    g = t.Generator("cuda").manual_seed(3)
+    tok = t.randn(2, 2, C, device="cuda", generator=g)
+    proj = t.randn(C, E, device="cuda", generator=g) * C ** -0.5
+    u8 = t.zeros(1, 16, 16, dtype=t.uint8, device="cuda")
+    u8[0, 2:13, 3:11] = 1
+    fr = gpu.FrameInput(tok, gpu.pack_masks(u8), 16, 16, 8, None)
+    want = gpu.embed_frames([fr], proj)[0].out
+    outs = gpu.embed_frames([fr] * n, proj)
+    assert t.equal(t.cat([o.out for o in outs]), want.expand(n, E))
