@@ -362,6 +362,7 @@ FrameDesc plan_frame(const FrameIn& f, int C, Shape& s, PlanAcc& a) {
     }
   }
   a.n_tiles += (f.m + 63) / 64 * (C / 64);
+  a.rows16 += (f.m + 15) / 16;
   return d;
 }
 
@@ -377,6 +378,7 @@ void finish_plan(Plan& p, const PlanAcc& a) {
   for (int j = 0; j < kLists; ++j) cap = std::max(cap, a.item_sub[j]);
   s.item_cap = (int)std::min<int64_t>(cap, INT32_MAX / 2 / kLists);
   s.n_tiles = a.n_tiles;
+  s.rows16 = a.rows16;
   choose_splits(s);
   p.L = make_layout(s);
 }
@@ -606,10 +608,14 @@ void tr_collect() {
 // one exists.
 // --------------------------------------------------------------------------
 namespace {
+// few: 0 where the form for few masks is not a candidate, else how many of a
+// mask tile's four 16-row parts hold masks on average (1 to 4): that form's
+// cost grows with them, the tiled forms' does not
 struct PoolKey {
-  int C, bf16, tok, n_tiles, split, kgroups;
+  int C, bf16, tok, n_tiles, split, kgroups, few;
   bool operator<(const PoolKey& o) const {
-    return std::tie(C, bf16, tok, n_tiles, split, kgroups) < std::tie(o.C, o.bf16, o.tok, o.n_tiles, o.split, o.kgroups);
+    return std::tie(C, bf16, tok, n_tiles, split, kgroups, few) <
+           std::tie(o.C, o.bf16, o.tok, o.n_tiles, o.split, o.kgroups, o.few);
   }
 };
 std::mutex g_tune_mu;
@@ -653,20 +659,22 @@ int pool_tile_choice(const Plan& p, int tok_dtype, const disc_options& o, bool t
     return o.pool_rows == 128 ? std::min(nt, 2) | (1 << 5) : nt;
   }
   const Shape& s = p.shape;
-  const PoolKey key{s.C, s.gemm_bf16, tok_dtype, s.n_tiles, s.pool_split, s.kgroups};
+  const int64_t mask_tiles = std::max(1, s.n_tiles / (s.C / 64));
+  const int few = pool_few_valid(b) ? (int)((s.rows16 + mask_tiles - 1) / mask_tiles) : 0;
+  const PoolKey key{s.C, s.gemm_bf16, tok_dtype, s.n_tiles, s.pool_split, s.kgroups, few};
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     const auto it = g_tune.find(key);
     if (it != g_tune.end()) return it->second;
   }
-  if (!tune) return pool_few_valid(b) && s.M <= 64 ? kPoolFew : pool_nt_rule(s);
+  if (!tune) return few && s.M <= 64 ? kPoolFew : pool_nt_rule(s);
   std::vector<int> cand;
   for (int uns = 0; uns < (s.pool_split > 1 ? 2 : 1); ++uns)
     for (int nt : {1, 2, 4})
       if (pool_nt_valid(s.C, nt)) cand.push_back(nt | (uns << 4));
   for (int nt : {1, 2})  // 128-mask workgroups, K never split
     if (pool_nt_valid(s.C, nt) && s.M > 64) cand.push_back(nt | (1 << 5));
-  if (pool_few_valid(b)) cand.push_back(kPoolFew);
+  if (few) cand.push_back(kPoolFew);
   std::vector<hipEvent_t> ev(4 * cand.size());
   for (auto& e : ev) (void)hipEventCreate(&e);
   for (size_t i = 0; i < cand.size(); ++i)

@@ -22,6 +22,7 @@ struct Shape {
   int n_frames = 0;
   int64_t M = 0, sumG = 0, sumMGs = 0;
   int C = 0, E = 0, gmax = 0, nchunk = 1, item_cap = 1, n_tiles = 0, gemm_bf16 = 0;
+  int64_t rows16 = 0;     // 16-row parts of the frames' mask tiles that hold masks
   int kgroups = 1;        // pooling K groups of the largest frame
   int pool_split = 1, proj_split = 1;
   bool want_dbar = false;  // some frame asks for the mean distinctiveness (needs r and its mean)
@@ -57,6 +58,7 @@ struct Plan {
 struct PlanAcc {
   int64_t M = 0, sumG = 0, sumMGs = 0;
   int64_t item_sub[kLists] = {};  // work-list capacity of each sub-list (masks g with g % kLists == j)
+  int64_t rows16 = 0;
   int gmax = 0, nchunk = 1, n_tiles = 0;
 };
 

@@ -67,6 +67,7 @@ Shape capacity_shape(const disc_server_config& c, int E, int gemm_bf16) {
   s.item_cap = (int)std::min<int64_t>(((int64_t)c.max_masks + kLists - 1) / kLists * ((c.max_w + 31) / 32 + 1) + 1,
                                       INT32_MAX / 2 / kLists);
   s.n_tiles = ((c.max_masks + 63) / 64 + c.max_frames) * (c.c / 64);
+  s.rows16 = (c.max_masks + 15) / 16 + c.max_frames;
   s.gemm_bf16 = gemm_bf16;
   s.want_dbar = true;  // any request may ask for the mean distinctiveness
   s.max_rows = c.max_h + 2;
