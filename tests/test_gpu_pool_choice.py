@@ -53,3 +53,21 @@ def test_choice_by_masks(gpu, C, order):
                 assert tiled and few, (n, m, names)
             else:
                 assert tiled != few, (n, m, names)
+
+
+@pytest.mark.parametrize("C,m", [(1280, 8), (1280, 120)])
+def test_first_call_work(gpu, C, m):
+    """A first call runs at most six forms twice, as many as there are without the one for few masks."""
+    t = torch()
+    g = t.Generator("cuda").manual_seed(C)
+    tok = t.randn(20, 20, C, device="cuda", generator=g)
+    proj = t.randn(C, 128, device="cuda", generator=g) * C ** -0.5
+    u8 = t.zeros(m, 160, 160, dtype=t.uint8, device="cuda")
+    u8[:, 30:110, 20:140] = 1
+    fr = gpu.FrameInput(tok, gpu.pack_masks(u8), 160, 160, 8, None)
+    t.cuda.synchronize()
+    with t.profiler.profile(activities=[t.profiler.ProfilerActivity.CUDA]) as p:
+        gpu.embed_frames([fr], proj)
+        t.cuda.synchronize()
+    n = sum(e.count for e in p.key_averages() if "k_pool<" in e.key or "k_pool_few" in e.key)
+    assert 2 <= n <= 12, [(e.key, e.count) for e in p.key_averages()]
