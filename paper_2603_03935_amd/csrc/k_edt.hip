@@ -1045,18 +1045,24 @@ __device__ __forceinline__ void direct_table(int cls, const uint32_t* recs, cons
 // hold: outward from the rows, four distances per step on both sides while any
 // row can still improve.
 __device__ __forceinline__ void search32(const uint2* base, int* best) {
-  auto gsq_of = [](int h) {  // g^2 decoded from C - T
-    const int t = edt_c(2) - h;
-    return t < 65025 ? t : (t - 64770) * (t - 64770);
+  // g^2 of two rows, decoded from C - T: T below 255^2, else (T - 64770)^2.  The
+  // square is not below T there and, taken of 0 at least, not above it before,
+  // so the larger is right without a choice.  (As a choice between the two the
+  // compiler branched for every entry: 32 masks of 720x1280, some with an inside
+  // more than 255 deep, whole launch 190 us, so 141.)
+  auto gsq_of = [](uint32_t h, int& a, int& b) {
+    const uint32_t t = ~h;  // 65535 - h
+    const us2 k = __builtin_elementwise_sub_sat(splat2(65535 - 64770), as_us2(h));
+    a = max((int)(t & 0xFFFFu), __mul24((int)k.x, (int)k.x));
+    b = max((int)(t >> 16), __mul24((int)k.y, (int)k.y));
   };
+  static_assert(edt_c(2) == 65535, "~h is C - h");
   int bmax = 0;
   const uint2 w = base[0];
-  const int g4[4] = {(int)(w.x & 0xFFFFu), (int)(w.x >> 16), (int)(w.y & 0xFFFFu), (int)(w.y >> 16)};
+  gsq_of(w.x, best[0], best[1]);
+  gsq_of(w.y, best[2], best[3]);
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    best[k] = gsq_of(g4[k]);
-    bmax = max(bmax, best[k]);
-  }
+  for (int k = 0; k < 4; ++k) bmax = max(bmax, best[k]);
   // d = 1 (mod 4): the windows start on words, up at u0 - d - 3, down at
   // u0 + d - 1 (one row early)
   for (int d = 1; d * d < bmax; d += 4) {
@@ -1066,14 +1072,10 @@ __device__ __forceinline__ void search32(const uint2* base, int* best) {
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
       const uint2 x = pu[q * 64], y = pd[q * 64];
-      su[4 * q] = gsq_of((int)(x.x & 0xFFFFu));
-      su[4 * q + 1] = gsq_of((int)(x.x >> 16));
-      su[4 * q + 2] = gsq_of((int)(x.y & 0xFFFFu));
-      su[4 * q + 3] = gsq_of((int)(x.y >> 16));
-      sd[4 * q] = gsq_of((int)(y.x & 0xFFFFu));
-      sd[4 * q + 1] = gsq_of((int)(y.x >> 16));
-      sd[4 * q + 2] = gsq_of((int)(y.y & 0xFFFFu));
-      sd[4 * q + 3] = gsq_of((int)(y.y >> 16));
+      gsq_of(x.x, su[4 * q], su[4 * q + 1]);
+      gsq_of(x.y, su[4 * q + 2], su[4 * q + 3]);
+      gsq_of(y.x, sd[4 * q], sd[4 * q + 1]);
+      gsq_of(y.y, sd[4 * q + 2], sd[4 * q + 3]);
     }
     bmax = 0;
 #pragma unroll
