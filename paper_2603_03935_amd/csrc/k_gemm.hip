@@ -593,9 +593,12 @@ bool pool_few_valid(const Batch& b) {
 }
 void launch_pool_few(const Batch& b, const Work& w, const int4* tiles, hipStream_t st) {
   if (b.n_tiles <= 0) return;
-  // with more wavefronts a workgroup's groups take one round; many masks fill the
-  // chip anyway and span few groups each
-  if (b.kgroups > 4 && b.M <= 64) hipLaunchKernelGGL(k_pool_few<8>, dim3(b.n_tiles * 16), dim3(512), 0, st, b, w, tiles);
+  // With eight wavefronts a workgroup's groups take half the rounds, but only
+  // one such workgroup fits a CU: for tiles that come to at most one each (12
+  // frames of 640 x 480 with 4 masks, served in one graph, eight / four
+  // wavefronts: 250 / 216 us; 8 masks of one frame at 2048 channels, 19 groups,
+  // 114 / 109).
+  if (b.kgroups > 4 && b.n_tiles <= 16) hipLaunchKernelGGL(k_pool_few<8>, dim3(b.n_tiles * 16), dim3(512), 0, st, b, w, tiles);
   else hipLaunchKernelGGL(k_pool_few<4>, dim3(b.n_tiles * 16), dim3(256), 0, st, b, w, tiles);
 }
 

@@ -71,3 +71,18 @@ def test_first_call_work(gpu, C, m):
         t.cuda.synchronize()
     n = sum(e.count for e in p.key_averages() if "k_pool<" in e.key or "k_pool_few" in e.key)
     assert 2 <= n <= 12, [(e.key, e.count) for e in p.key_averages()]
+
+
+def test_wavefronts(gpu):
+    """Beyond one workgroup per CU the form for few masks runs with four wavefronts each."""
+    t = torch()
+    C = 896
+    g = t.Generator("cuda").manual_seed(C)
+    tok = t.randn(36, 36, C, device="cuda", generator=g)  # six K groups
+    proj = t.randn(C, 128, device="cuda", generator=g) * C ** -0.5
+    u8 = t.zeros(4, 288, 288, dtype=t.uint8, device="cuda")
+    u8[:, 30:210, 20:240] = 1
+    fr = gpu.FrameInput(tok, gpu.pack_masks(u8), 288, 288, 8, None)
+    for n, form in ((1, "k_pool_few<8>"), (12, "k_pool_few<4>")):
+        names = _kernels(lambda: gpu.embed_frames([fr] * n, proj))  # a first call: every form runs
+        assert [x for x in ("k_pool_few<4>", "k_pool_few<8>") if any(x in y for y in names)] == [form]
