@@ -642,6 +642,19 @@ int pool_nt_rule(const Shape& s) {
     if (pool_nt_valid(s.C, nt) && s.n_tiles / nt * s.pool_split >= 4 * kTargetWGs) return nt;
   return 1;
 }
+// Untimed, up to 64 masks: the form for few masks.  Of one frame it takes as
+// many groups as its wavefronts hold in a round, four or, up to 1024 channels,
+// eight; beyond, the tiled form spreads a tile's groups over more workgroups
+// (whole calls of 8 to 64 masks, few against tiled: 2 to 4 groups -15 to -2 %,
+// 5 to 8 groups -14 to 0 % up to 1024 channels and -7 to +13 % above, 9 and 10
+// groups -8 to +7 % and -1 to +21 %, 19 groups 0 to +15 %, 57 groups up to
+// +60 %).  One mask spans few of its frame's groups (-16 to 0 % at any number).
+// Where several frames may come, the tiles of all leave the tiled form few
+// workgroups each (one frame of 640 x 480 with 8 masks, served by a graph for
+// 16 frames, 135 tiled / 116 us).
+bool pool_few_rule(const Shape& s, int few) {
+  return few && s.M <= 64 && (s.n_frames > 1 || s.M == 1 || s.kgroups <= (s.C <= 1024 ? 8 : 4));
+}
 }  // namespace
 
 // The pooling launch of a problem shape: channels per workgroup (NT x 64),
@@ -667,7 +680,7 @@ int pool_tile_choice(const Plan& p, int tok_dtype, const disc_options& o, bool t
     const auto it = g_tune.find(key);
     if (it != g_tune.end()) return it->second;
   }
-  if (!tune) return few && s.M <= 64 ? kPoolFew : pool_nt_rule(s);
+  if (!tune) return pool_few_rule(s, few) ? kPoolFew : pool_nt_rule(s);
   // With the form for few masks a candidate, two that lose there are not timed,
   // so that a first call runs no more forms than without it: 256 channels a
   // workgroup with K unsplit beside a split one (a quarter of tiles too few to

@@ -86,3 +86,19 @@ def test_wavefronts(gpu):
     for n, form in ((1, "k_pool_few<8>"), (12, "k_pool_few<4>")):
         names = _kernels(lambda: gpu.embed_frames([fr] * n, proj))  # a first call: every form runs
         assert [x for x in ("k_pool_few<4>", "k_pool_few<8>") if any(x in y for y in names)] == [form]
+
+
+@pytest.mark.parametrize("C,side,m,few", [(960, 360, 8, True), (960, 368, 8, False), (1088, 256, 64, True),
+                                          (1088, 264, 64, False), (1088, 560, 1, True)])
+def test_untimed(gpu, C, side, m, few):
+    """The rule of untimed calls: 8 and 9 groups of 256 patches, 4 and 5 beyond 1024 channels, one mask."""
+    t = torch()
+    g = t.Generator("cuda").manual_seed(C)
+    n = side // 8
+    tok = t.randn(n, n, C, device="cuda", generator=g)
+    proj = t.randn(C, 128, device="cuda", generator=g) * C ** -0.5
+    u8 = t.zeros(m, side, side, dtype=t.uint8, device="cuda")
+    u8[:, 30:210, 20:140] = 1
+    fr = gpu.FrameInput(tok, gpu.pack_masks(u8), side, side, 8, None)
+    names = _kernels(lambda: gpu.embed_masks_noalloc(fr, proj))
+    assert any("k_pool_few" in x for x in names) == few and any("k_pool<" in x for x in names) != few
