@@ -503,6 +503,39 @@ __global__ __launch_bounds__(256) void k_db_fill(const float* pts, int n, DbWork
   d.spts[d.range[d.slot[i]].x + d.rank[i]] = make_float4(p[0], p[1], p[2], __int_as_float(i));
 }
 
+// A thread per sorted position t, for grids of mostly lone points: its cell,
+// then the 26 around it, look-up after look-up, until the test is settled.
+template <int PASS>
+__device__ __forceinline__ void db_point(const DbWork& d, int t, float e2, int min_pts, int32_t* keep) {
+#pragma clang fp contract(off)
+  if (PASS == 1 && d.core[t]) return;
+  const float4 p = d.spts[t];
+  const int i = __float_as_int(p.w);
+  const uint64_t key = d.keys[d.slot[i]];
+  const int x = (int)((key >> 32) & 0xFFFF) - 32768, y = (int)((key >> 16) & 0xFFFF) - 32768,
+            z = (int)(key & 0xFFFF) - 32768;
+  // (as in k_db_cells: at the edge of the key range each distinct cell once)
+  auto rep = [](int v, int dd) { return dd > -1 && cell16(v + dd) == cell16(v + dd - 1); };
+  const int want = PASS == 0 ? min_pts : 1;
+  int found = 0;
+  for (int k = 0; k < 27 && found < want; ++k) {
+    const int c = k == 0 ? 13 : (k <= 13 ? k - 1 : k);  // the own cell first
+    const int dz = c / 9 - 1, dy = c / 3 % 3 - 1, dx = c % 3 - 1;
+    if (rep(z, dz) || rep(y, dy) || rep(x, dx)) continue;
+    const int h = hash_find(d.keys, d.mask, cell_key((int)(key >> 48), x + dx, y + dy, z + dz));
+    if (h < 0) continue;
+    const int2 r = d.range[h];
+    for (int j = r.x; j < r.x + r.y && found < want; ++j) {
+      const float4 q = d.spts[j];
+      const float ax = p.x - q.x, ay = p.y - q.y, az = p.z - q.z;
+      if ((ax * ax + ay * ay) + az * az <= e2 && (PASS == 0 || d.core[j])) ++found;
+    }
+  }
+  const int r = found >= want ? 1 : 0;
+  if (PASS == 0) d.core[t] = (uint8_t)r;
+  keep[i] = r;
+}
+
 // A wavefront per work item: up to 64 points of one cell against the points
 // of the 27 cells around it.  Points of cells are loaded 64 at a time, one per
 // lane, and each point of the item that is not settled yet is broadcast and
@@ -520,12 +553,25 @@ __global__ __launch_bounds__(256) void k_db_fill(const float* pts, int n, DbWork
 // point that walked its 27 cells by itself, one dependent load after the
 // other and as long as the slowest of its wavefront, took 213 + 62 us for 180k
 // points (eps 3 cm, 8 points), this 36 + 12 us.
+//
+// Where most cells hold a few points, there are too many items, each a chain of
+// loads for a handful of tests: then a thread per point (db_point), whose own
+// chain of 27 look-ups is the longer one but runs 64 to a wavefront.  The line
+// is where the items' chains outlast one round of the points' (us, 4 points,
+// items / points: 100k points in 63k cells 129 / 142, in 88k 190 / 170; 300k in
+// 130k 195 / 154, in 74k 115 / 110; 1M in 246k 286 / 223, in 317k 371 / 271; a
+// thread per point always 152, 212; 204, 153; 306, 356 before there were
+// items); min_pts = 1 is settled by the point itself.
 template <int PASS>
-__global__ __launch_bounds__(256) void k_db_cells(DbWork d, float eps, int min_pts, int32_t* keep) {
+__global__ __launch_bounds__(256) void k_db_cells(DbWork d, int n, float eps, int min_pts, int32_t* keep) {
 #pragma clang fp contract(off)
   const int lane = threadIdx.x & 63;
   const int nitems = d.total[1];
   const float e2 = eps * eps;
+  if (nitems > (min_pts == 1 ? 10000 : 30000 + n / 4)) {
+    for (int t = blockIdx.x * 256 + threadIdx.x; t < n; t += gridDim.x * 256) db_point<PASS>(d, t, e2, min_pts, keep);
+    return;
+  }
   // offset + 1 of lane c's cell along each axis, two bits per lane, in the order own cell, 6 faces, 12 edges, 8 corners
   constexpr int kOrder[27][3] = {
       {1, 1, 1}, {0, 1, 1}, {2, 1, 1}, {1, 0, 1}, {1, 2, 1}, {1, 1, 0}, {1, 1, 2}, {0, 0, 1}, {0, 2, 1},
@@ -1110,11 +1156,11 @@ void launch_dbscan(const float* pts, const int32_t* off, int m, int n, float eps
   hipLaunchKernelGGL(k_db_insert, dim3(nb), dim3(256), 0, st, pts, off, m, n, eps, d);
   hipLaunchKernelGGL(k_db_alloc, dim3((T + 4095) / 4096), dim3(1024), 0, st, d, T);
   hipLaunchKernelGGL(k_db_fill, dim3(nb), dim3(256), 0, st, pts, n, d);
-  // at most one work item per point and one per 64; eight workgroups per CU
-  // take what there is in turn
-  const int ng = std::min(nb * 64 + 1, 8 * 256);
-  hipLaunchKernelGGL(k_db_cells<0>, dim3(ng), dim3(256), 0, st, d, eps, min_pts, keep);
-  hipLaunchKernelGGL(k_db_cells<1>, dim3(ng), dim3(256), 0, st, d, eps, min_pts, keep);
+  // at most one work item per point and one per 64; eight workgroups per CU, or
+  // one per 256 points, take what there is in turn
+  const int ng = std::min(nb * 64 + 1, std::max(nb, 8 * 256));
+  hipLaunchKernelGGL(k_db_cells<0>, dim3(ng), dim3(256), 0, st, d, n, eps, min_pts, keep);
+  hipLaunchKernelGGL(k_db_cells<1>, dim3(ng), dim3(256), 0, st, d, n, eps, min_pts, keep);
 }
 
 static size_t voxel_carve(char* ws, int n, int m, VoxWork& d) {
