@@ -391,6 +391,12 @@ __device__ __forceinline__ uint64_t max64(uint64_t a, uint64_t b) { return a > b
 // past the last) go to kout.
 constexpr int kTopkThreads = 1024;
 constexpr int kTopkCand = 2048;
+// Rows of up to 2048 elements, k <= 64: 256 threads, a group each, so that eight
+// rows share a CU instead of two (whole calls at width 64, 1024 / 256 threads:
+// 4000 rows of 300, k = 1 39.5 / 20.2 us, k = 64 44.9 / 22.4, 20000 of 2000 214 /
+// 116, 64 of 2000 17 / 17; k passes over the row took 135 us for 20000 of 400
+// and k = 1 at width 512, 1024 threads 228).
+constexpr int kTopkFew = 256;
 // elements per workgroup of the widest level-0 kernel: one level covers a row
 // of up to 32768 (20011 elements: 9 us; in four chunks and a second level, 15)
 constexpr int kTopkRow = 32 * kTopkThreads;
@@ -417,13 +423,14 @@ __device__ __forceinline__ uint64_t topk_threshold(const uint64_t* gk, int k) {
   return T;
 }
 
-template <int VPT, int KEYS, int FINAL>
-__global__ __launch_bounds__(kTopkThreads) void k_topk(const float* sim, const uint64_t* kin, int n, int k, int nch,
+template <int VPT, int KEYS, int FINAL, int NT = kTopkThreads>
+__global__ __launch_bounds__(NT) void k_topk(const float* sim, const uint64_t* kin, int n, int k, int nch,
                                                        uint64_t* kout, float* scores, int32_t* idx) {
   const int64_t j = blockIdx.x / nch;
-  const int c0 = (int)(blockIdx.x % nch) * (kTopkThreads * VPT), tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  __shared__ uint64_t gk[kTopkThreads];
-  __shared__ uint64_t cand[kTopkCand];
+  constexpr int kCand = NT == kTopkThreads ? kTopkCand : 2 * NT;
+  const int c0 = (int)(blockIdx.x % nch) * (NT * VPT), tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  __shared__ uint64_t gk[NT];
+  __shared__ uint64_t cand[kCand];
   __shared__ uint64_t Tsh;
   __shared__ int nc_sh;
   uint64_t key[VPT];
@@ -431,7 +438,7 @@ __global__ __launch_bounds__(kTopkThreads) void k_topk(const float* sim, const u
     const uint64_t* row = kin + j * n;
 #pragma unroll
     for (int r = 0; r < VPT; ++r) {
-      const int i = c0 + r * kTopkThreads + tid;
+      const int i = c0 + r * NT + tid;
       key[r] = i < n ? row[i] : 0ull;
     }
   } else {
@@ -439,19 +446,19 @@ __global__ __launch_bounds__(kTopkThreads) void k_topk(const float* sim, const u
     float v[VPT];
 #pragma unroll
     for (int r = 0; r < VPT; ++r) {
-      const int i = c0 + r * kTopkThreads + tid;
+      const int i = c0 + r * NT + tid;
       v[r] = i < n ? row[i] : 0.f;
     }
 #pragma unroll
     for (int r = 0; r < VPT; ++r) {
-      const int i = c0 + r * kTopkThreads + tid;
+      const int i = c0 + r * NT + tid;
       key[r] = i < n ? rank_key(v[r], i) : 0ull;
     }
   }
   uint64_t best = 0;
 #pragma unroll
   for (int r = 0; r < VPT; ++r) best = max64(best, key[r]);
-  const bool wide = k > 64;  // uniform
+  const bool wide = NT == kTopkFew || k > 64;  // uniform
   if (!wide) {
     best = max64(best, __shfl_xor(best, 1));
     best = max64(best, __shfl_xor(best, 2));
@@ -462,7 +469,7 @@ __global__ __launch_bounds__(kTopkThreads) void k_topk(const float* sim, const u
   if (tid == 0) nc_sh = 0;
   __syncthreads();
   if (wv == 0) {
-    const uint64_t T = wide ? topk_threshold<kTopkThreads / 64>(gk, k) : topk_threshold<4>(gk, k);
+    const uint64_t T = wide ? topk_threshold<NT / 64>(gk, k) : topk_threshold<4>(gk, k);
     if (lane == 0) Tsh = T;
   }
   __syncthreads();
@@ -471,7 +478,7 @@ __global__ __launch_bounds__(kTopkThreads) void k_topk(const float* sim, const u
   for (int r = 0; r < VPT; ++r)
     if (key[r] >= T) {
       const int p = atomicAdd(&nc_sh, 1);
-      if (p < kTopkCand) cand[p] = key[r];
+      if (p < kCand) cand[p] = key[r];
     }
   __syncthreads();
   const int nc = nc_sh;
@@ -484,15 +491,15 @@ __global__ __launch_bounds__(kTopkThreads) void k_topk(const float* sim, const u
       kout[o + rank] = q;
     }
   };
-  if (nc <= kTopkCand) {
-    for (int c = tid; c < nc; c += kTopkThreads) {
+  if (nc <= kCand) {
+    for (int c = tid; c < nc; c += NT) {
       const uint64_t q = cand[c];
       int rank = 0;
 #pragma unroll 4
       for (int i = 0; i < nc; ++i) rank += cand[i] > q ? 1 : 0;
       if (rank < k) emit(rank, q);
     }
-    for (int r = nc + tid; r < k; r += kTopkThreads) emit(r, 0ull);
+    for (int r = nc + tid; r < k; r += NT) emit(r, 0ull);
   } else {
     uint64_t last = ~0ull;
     for (int r = 0; r < k; ++r) {
@@ -503,7 +510,7 @@ __global__ __launch_bounds__(kTopkThreads) void k_topk(const float* sim, const u
       for (int s = 32; s > 0; s >>= 1) top = max64(top, __shfl_xor(top, s));
       if (lane == 0) gk[wv] = top;
       __syncthreads();
-      for (int w = 0; w < kTopkThreads / 64; ++w) top = max64(top, gk[w]);
+      for (int w = 0; w < NT / 64; ++w) top = max64(top, gk[w]);
       __syncthreads();
       if (tid == 0) emit(r, top);
       last = top;
@@ -529,6 +536,10 @@ static void launch_topk_rows(const float* sim, int m, int q, int k, uint64_t* ka
   const int nch = topk_chunks(m, kTopkRow);
   const dim3 blk(kTopkThreads);
   if (nch == 1) {
+    if (m <= 8 * kTopkFew && k <= 64) {
+      hipLaunchKernelGGL((k_topk<8, 0, 1, kTopkFew>), dim3(q), dim3(kTopkFew), 0, st, sim, nullptr, m, k, 1, nullptr, scores, idx);
+      return;
+    }
     // a row of at most 8192 leaves three quarters of the wide kernel's registers empty
     if (m <= 8 * kTopkThreads) hipLaunchKernelGGL((k_topk<8, 0, 1>), dim3(q), blk, 0, st, sim, nullptr, m, k, 1, nullptr, scores, idx);
     else hipLaunchKernelGGL((k_topk<32, 0, 1>), dim3(q), blk, 0, st, sim, nullptr, m, k, 1, nullptr, scores, idx);
