@@ -26,6 +26,7 @@
 //                    two lists whose boxes meet are taken, the more entries are
 //                    staged in LDS and the fewer binary-searched there.
 #include <algorithm>
+#include <type_traits>
 
 #include "disc_device.h"
 
@@ -877,7 +878,11 @@ __device__ __forceinline__ uint64_t vox_code3(int x, int y, int z) {
 // coordinates within +-2^20 (the voxel sets above are within +-32767).
 //
 // 1296 pairs of 36 x 36 lists of up to 9000 voxels: 75 us with every pair's
-// longer list read by 256 threads, 29 us by boxes and 6 us to make them.
+// longer list read by 256 threads, 29 us by boxes and 6 us to make them.  Of
+// short lists a thread takes one, two or four entries: with eight always, 1600
+// pairs of 200 voxels took 16.4 us a call and 10000 of 100 36, so 13.6 and 24.
+// (The boxes' launch is not worth its 3 us there: 10.5 and 17 without boxes, by
+// 256 threads; the host does not know the lists' lengths.)
 constexpr int kOvParts = 32;
 struct VoxBox {
   int32_t lo[3], hi[3];
@@ -913,7 +918,7 @@ __global__ __launch_bounds__(1024) void k_vox_boxes(const int32_t* va, const int
     boxes[(int64_t)i * kOvParts + r] = VoxBox{{lo[0], lo[1], lo[2]}, {hi[0], hi[1], hi[2]}};
 }
 
-constexpr int kOvPer = 8;  // entries per thread and round, loaded together
+constexpr int kOvPer = 8;  // entries per thread and round, loaded together (1, 2 or 4 where they cover the list)
 constexpr int kOvChunk = 512 * kOvPer;
 
 // The runs of a list that take part, as one list of n entries: pre[r] entries
@@ -995,42 +1000,57 @@ __global__ __launch_bounds__(512) void k_overlap(const int32_t* va, const int32_
   const bool swap = n0 > n1;  // the keys are those of the list with fewer entries
   const int32_t *kl = swap ? vb : va, *tl = swap ? va : vb;
   const int kb = swap ? b0 : a0, tb = swap ? a0 : b0, nk = swap ? n1 : n0, nt = swap ? n0 : n1;
-  // codes of entries t0 + 64 u + lane of a list that takes part, `past` for those beyond its n entries
-  auto load = [&](const int32_t* l, int base, const OvRuns& o, int n, int t0, uint64_t past, uint64_t (&code)[kOvPer]) {
+  // f with the number of entries per thread (1, 2, 4 or 8) that covers n entries, or a whole chunk
+  auto per_thread = [&](int n, auto f) {
+    if (n <= 512) f(std::integral_constant<int, 1>{});
+    else if (n <= 1024) f(std::integral_constant<int, 2>{});
+    else if (n <= 2048) f(std::integral_constant<int, 4>{});
+    else f(std::integral_constant<int, kOvPer>{});
+  };
+  // codes of entries t0 + 512 u of a list that takes part, `past` for those beyond its n entries
+  auto load = [&](auto u, const int32_t* l, int base, const OvRuns& o, int n, int t0, uint64_t past, uint64_t* code) {
 #pragma unroll
-    for (int u = 0; u < kOvPer; ++u) {
-      const int t = min(t0 + 64 * u + lane, n - 1);
+    for (int k = 0; k < decltype(u)::value; ++k) {
+      const int t = min(t0 + 512 * k, n - 1);
       const int32_t* v = l + 3 * (int64_t)(BOXES ? ov_entry(o, t) : base + t);
       const uint64_t c = vox_code3(v[0], v[1], v[2]);
-      code[u] = t0 + 64 * u + lane < n ? c : past;
+      code[k] = t0 + 512 * k < n ? c : past;
     }
   };
-  uint64_t code[kOvPer];
   int cnt = 0;
   if (nk > 0) {
     for (int c0 = 0; c0 < nt; c0 += kOvChunk) {
-      load(tl, tb, runs[swap ? 0 : 1], nt, c0 + 64 * kOvPer * wv, ~1ull, code);  // past the end: above every code, equal to no key
-      __syncthreads();
+      int len = 0;  // staged codes, a power of two
+      per_thread(nt - c0, [&](auto u) {
+        constexpr int U = decltype(u)::value;
+        uint64_t code[U];
+        load(u, tl, tb, runs[swap ? 0 : 1], nt, c0 + tid, ~1ull, code);  // past the end: above every code, equal to no key
+        __syncthreads();
 #pragma unroll
-      for (int u = 0; u < kOvPer; ++u) sb[64 * (kOvPer * wv + u) + lane] = code[u];
+        for (int k = 0; k < U; ++k) sb[512 * k + tid] = code[k];
+        len = 512 * U;
+      });
       __syncthreads();
       const uint64_t first = sb[0], last = sb[min(kOvChunk, nt - c0) - 1];
-      for (int k0 = 64 * kOvPer * wv; k0 < nk; k0 += kOvChunk) {
-        load(kl, kb, runs[swap ? 1 : 0], nk, k0, ~0ull, code);
-        bool any = false;
+      for (int k0 = 0; k0 < nk; k0 += kOvChunk)
+        per_thread(nk - k0, [&](auto u) {
+          constexpr int U = decltype(u)::value;
+          uint64_t code[U];
+          load(u, kl, kb, runs[swap ? 1 : 0], nk, k0 + tid, ~0ull, code);
+          bool any = false;
 #pragma unroll
-        for (int u = 0; u < kOvPer; ++u) any |= code[u] >= first && code[u] <= last;
-        if (__ballot(any) == 0) continue;
-        int at[kOvPer];  // entries below the key (one less if all are); the searches advance together
+          for (int k = 0; k < U; ++k) any |= code[k] >= first && code[k] <= last;
+          if (__ballot(any) == 0) return;
+          int at[U];  // entries below the key (one less if all are); the searches advance together
 #pragma unroll
-        for (int u = 0; u < kOvPer; ++u) at[u] = 0;
-        for (int step = kOvChunk / 2; step > 0; step >>= 1) {
+          for (int k = 0; k < U; ++k) at[k] = 0;
+          for (int step = len / 2; step > 0; step >>= 1) {
 #pragma unroll
-          for (int u = 0; u < kOvPer; ++u) at[u] += sb[at[u] + step - 1] < code[u] ? step : 0;
-        }
+            for (int k = 0; k < U; ++k) at[k] += sb[at[k] + step - 1] < code[k] ? step : 0;
+          }
 #pragma unroll
-        for (int u = 0; u < kOvPer; ++u) cnt += sb[at[u]] == code[u] ? 1 : 0;
-      }
+          for (int k = 0; k < U; ++k) cnt += sb[at[k]] == code[k] ? 1 : 0;
+        });
     }
   }
   for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o);
