@@ -45,10 +45,8 @@ __device__ __forceinline__ uint64_t valid_bits(int k, int wq, int w) {
   return (k == wq - 1 && (w & 63)) ? ((1ull << (w & 63)) - 1) : ~0ull;
 }
 
-// mask pixels in an unbroken run ending at column x (inclusive), going left;
-// the walk stops once the count reaches cap (the result is then >= cap, not
-// the run's length: callers that clamp g at cap or below lose nothing)
-__device__ __forceinline__ int run_left(const uint64_t* row, int x, int wq, int w, int cap = INT32_MAX) {
+// mask pixels in an unbroken run ending at column x (inclusive), going left
+__device__ __forceinline__ int run_left(const uint64_t* row, int x, int wq, int w) {
   if (x < 0) return 0;
   int k = x >> 6;
   const int bpos = x & 63;
@@ -56,7 +54,7 @@ __device__ __forceinline__ int run_left(const uint64_t* row, int x, int wq, int 
   const uint64_t z = ~wd & ((2ull << bpos) - 1);
   if (z) return bpos - 63 + __builtin_clzll(z);
   int L = bpos + 1;
-  for (--k; k >= 0 && L < cap; --k) {
+  for (--k; k >= 0; --k) {
     wd = row[k];
     if (~wd) return L + __builtin_clzll(~wd);
     L += 64;
@@ -64,9 +62,8 @@ __device__ __forceinline__ int run_left(const uint64_t* row, int x, int wq, int 
   return L;
 }
 
-// mask pixels in an unbroken run starting at column x, going right (the walk
-// stops at cap as in run_left)
-__device__ __forceinline__ int run_right(const uint64_t* row, int x, int wq, int w, int cap = INT32_MAX) {
+// mask pixels in an unbroken run starting at column x, going right
+__device__ __forceinline__ int run_right(const uint64_t* row, int x, int wq, int w) {
   if (x >= w) return 0;
   int k = x >> 6;
   const int bpos = x & 63;
@@ -74,7 +71,7 @@ __device__ __forceinline__ int run_right(const uint64_t* row, int x, int wq, int
   const uint64_t z = ~wd & (~0ull << bpos);
   if (z) return __builtin_ctzll(z) - bpos;
   int R = 64 - bpos;
-  for (++k; k < wq && R < cap; ++k) {
+  for (++k; k < wq; ++k) {
     wd = row[k] & valid_bits(k, wq, w);
     if (~wd) return R + __builtin_ctzll(~wd);
     R += 64;

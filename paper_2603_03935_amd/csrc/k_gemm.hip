@@ -76,13 +76,6 @@ constexpr int PAS = PBK + 8;  // LDS row stride (elements) of A and B
 // rows with one chunk) see the same bank pattern as without the swizzle.
 __device__ __forceinline__ int bsw(int row, int chunk) { return chunk ^ ((row >> 4) & 3); }
 
-template <int TOK>
-__device__ __forceinline__ uint16_t tok_bf16(const void* base, int64_t off) {
-  if (TOK == 0) return f2bf(reinterpret_cast<const float*>(base)[off]);
-  if (TOK == 1) return reinterpret_cast<const uint16_t*>(base)[off];
-  return (uint16_t)(__float_as_uint(e4m3x4_to_f32(reinterpret_cast<const uint8_t*>(base)[off]).x) >> 16);
-}
-
 // K range [kbeg, kend) of a tile: the union of its masks' patch-row ranges
 // (rows of patches outside every mask's box hold zero weights for all of them).
 // Tile row i of a frame holds mask perm[mask_base + i] (masks ordered by the

@@ -36,7 +36,7 @@ namespace disc {
 // prefix sums
 // ---------------------------------------------------------------------------
 // sum of v over the threads before this one of a block of 1024, the block's
-// sum in total; sh: 17 values.  Every thread of the block calls it.
+// sum in total; sh: 16 values.  Every thread of the block calls it.
 template <class T>
 __device__ __forceinline__ T block_exscan_1024(T v, T* sh, T& total) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;

@@ -12,23 +12,6 @@ namespace disc {
 
 
 
-// e4m3fn code -> BF16 bits of the same value (exact: e4m3 values are BF16 values)
-
-// four consecutive channels of token p as floats (value = scale * code for FP8)
-__device__ __forceinline__ float4 load4(const void* base, int dtype, const float* scale, int64_t p, int C, int c) {
-  const int64_t off = p * C + c;
-  if (dtype == 0) return *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(base) + off);
-  if (dtype == 1) {
-    const uint2 v = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(base) + off);
-    return make_float4(bf16_to_f32(v.x & 0xFFFFu), bf16_to_f32(v.x >> 16), bf16_to_f32(v.y & 0xFFFFu),
-                       bf16_to_f32(v.y >> 16));
-  }
-  const uint32_t v = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const uint8_t*>(base) + off);
-  const float s = scale[p];
-  const float4 x = e4m3x4_to_f32(v);
-  return make_float4(s * x.x, s * x.y, s * x.z, s * x.w);
-}
-
 // Partial channel sums of one (frame, chunk): colsum_chunk (the device
 // helpers header); a standalone launch, or workgroups of the mask scan's
 // launch for small batches.
