@@ -37,12 +37,16 @@
  *   - m == 0 masks is a no-op that returns DISC_OK.
  *   - Calls on different streams may run concurrently; the library keeps one
  *     workspace per (device, stream) unless the caller passes its own.
- *   - Stream capture: the entry points that take a stream stage their
- *     descriptors through a host buffer that the next call reuses (and may
- *     time tuning candidates or grow a workspace), so they refuse a stream
+ *     hipStreamPerThread, one handle for every thread's stream, counts as one
+ *     stream: calls on it that use the workspace must be ordered by the caller.
+ *   - Stream capture: a call that keeps the library's workspace may have to
+ *     grow it, may time tuning candidates, and stages more than eight frames
+ *     through a host buffer that the next call reuses, so it refuses a stream
  *     that is being captured (DISC_ERR_INVALID_ARGUMENT, nothing enqueued).
- *     disc_embed_masks_noalloc enqueues kernels only and can be captured;
- *     the serving runtime captures its own graphs.
+ *     disc_embed_masks_noalloc, disc_pack_masks, disc_view_quality,
+ *     disc_angle_score, disc_backproject and disc_voxel_overlap enqueue
+ *     kernels only and can be captured; the serving runtime captures its own
+ *     graphs.
  *
  * Layouts:
  *   tokens  [gh][gw][c] row-major, c fastest; gh = ceil(h/patch), gw = ceil(w/patch)
@@ -252,8 +256,11 @@ disc_status disc_query_topk(const float* emb, int32_t m, const void* text, int32
  * P the projection [c][e], D_p of Eq. (1) with epsilon eps; 0 where text_j
  * or y_p is the zero vector.  |heat| <= D_p.
  *   text [q][e] (text_dtype DISC_F32 or DISC_BF16), heat [q][gh*gw] FP32
- *   written, patch-row-major.  FP32 arithmetic (tokens and P widened
- *   exactly), FP32 accumulation.
+ *   written, patch-row-major.  Tokens, P and text enter as they are, none
+ *   rounded: BF16 or FP8 tokens with a BF16 P as operands of BF16 matrix
+ *   instructions, whose products are exact, all others widened to FP32.  Sums
+ *   are FP32; the FP8 scale of a token multiplies y_p as a whole on the BF16
+ *   path and each of its elements on the other.
  * Device pointers, 16-byte aligned; 0 <= q <= 2^20 (0: no-op); eps >= 0.
  * Invalid arguments: nothing is enqueued, DISC_ERR_* is returned.
  * Asynchronous on `stream`. */
@@ -358,8 +365,7 @@ disc_status disc_dbscan_denoise(const float* points, const int32_t* offsets, int
  *   voxels [n][3] int32 (capacity n rows; rows [voffsets[i], voffsets[i+1])
  *   written), status [m] int32 or NULL: 0 ok, 1 some point's voxel lies
  *   beyond +-32767 per axis (the point is left out).  Any number of voxels
- *   per segment (beyond 8192 the segment is sorted in chunks and merged by
- *   rank, within its workgroup).
+ *   per segment (they are sorted in chunks of 1024, which are merged by rank).
  * n <= 2^23, m <= 65535, voxel > 0.  Asynchronous on `stream`. */
 disc_status disc_voxelize(const float* points, const int32_t* offsets, const int32_t* keep, int32_t m, int32_t n,
                           float voxel, int32_t* voffsets, int32_t* voxels, int32_t* status, void* stream);

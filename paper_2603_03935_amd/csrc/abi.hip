@@ -214,13 +214,14 @@ struct Ctx {
 };
 
 disc_status acquire(hipStream_t st, const Layout& L, const disc_options* opts, Ctx& cx) {
-  // The staged descriptors go through a host buffer that the next call on
-  // this stream reuses, and a new shape may time the pooling candidates or
-  // grow the workspace: none of that may be recorded into a graph.
+  // This call may grow the workspace, a new shape may time the pooling
+  // candidates, and more than kStageFrames descriptors go through a host buffer
+  // that the next call on this stream reuses: none of that may be recorded into
+  // a graph.
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(st, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone)
     return fail(DISC_ERR_INVALID_ARGUMENT,
-                "the stream is being captured: this entry point stages through a reused host buffer; "
+                "the stream is being captured: this entry point may grow its workspace or time kernels; "
                 "capture disc_embed_masks_noalloc instead");
   hipError_t e = hipGetDevice(&cx.dev);
   if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
