@@ -880,7 +880,7 @@ __device__ __forceinline__ uint64_t vox_code3(int x, int y, int z) {
 // 1296 pairs of 36 x 36 lists of up to 9000 voxels: 75 us with every pair's
 // longer list read by 256 threads, 29 us by boxes and 6 us to make them.  Of
 // short lists a thread takes one, two or four entries: with eight always, 1600
-// pairs of 200 voxels took 16.4 us a call and 10000 of 100 36, so 13.6 and 24.
+// pairs of 200 voxels took 16.4 us a call and 10000 of 100 36, so 13.4 and 29.
 // (The boxes' launch is not worth its 3 us there: 10.5 and 17 without boxes, by
 // 256 threads; the host does not know the lists' lengths.)
 constexpr int kOvParts = 32;
@@ -1007,14 +1007,14 @@ __global__ __launch_bounds__(512) void k_overlap(const int32_t* va, const int32_
     else if (n <= 2048) f(std::integral_constant<int, 4>{});
     else f(std::integral_constant<int, kOvPer>{});
   };
-  // codes of entries t0 + 512 u of a list that takes part, `past` for those beyond its n entries
+  // codes of entries t0 + 64 u of a list that takes part, `past` for those beyond its n entries
   auto load = [&](auto u, const int32_t* l, int base, const OvRuns& o, int n, int t0, uint64_t past, uint64_t* code) {
 #pragma unroll
     for (int k = 0; k < decltype(u)::value; ++k) {
-      const int t = min(t0 + 512 * k, n - 1);
+      const int t = min(t0 + 64 * k, n - 1);
       const int32_t* v = l + 3 * (int64_t)(BOXES ? ov_entry(o, t) : base + t);
       const uint64_t c = vox_code3(v[0], v[1], v[2]);
-      code[k] = t0 + 512 * k < n ? c : past;
+      code[k] = t0 + 64 * k < n ? c : past;
     }
   };
   int cnt = 0;
@@ -1024,10 +1024,11 @@ __global__ __launch_bounds__(512) void k_overlap(const int32_t* va, const int32_
       per_thread(nt - c0, [&](auto u) {
         constexpr int U = decltype(u)::value;
         uint64_t code[U];
-        load(u, tl, tb, runs[swap ? 0 : 1], nt, c0 + tid, ~1ull, code);  // past the end: above every code, equal to no key
+        const int e0 = 64 * U * wv + lane;  // a wavefront's entries are consecutive
+        load(u, tl, tb, runs[swap ? 0 : 1], nt, c0 + e0, ~1ull, code);  // past the end: above every code, equal to no key
         __syncthreads();
 #pragma unroll
-        for (int k = 0; k < U; ++k) sb[512 * k + tid] = code[k];
+        for (int k = 0; k < U; ++k) sb[64 * k + e0] = code[k];
         len = 512 * U;
       });
       __syncthreads();
@@ -1036,7 +1037,7 @@ __global__ __launch_bounds__(512) void k_overlap(const int32_t* va, const int32_
         per_thread(nk - k0, [&](auto u) {
           constexpr int U = decltype(u)::value;
           uint64_t code[U];
-          load(u, kl, kb, runs[swap ? 1 : 0], nk, k0 + tid, ~0ull, code);
+          load(u, kl, kb, runs[swap ? 1 : 0], nk, k0 + 64 * U * wv + lane, ~0ull, code);
           bool any = false;
 #pragma unroll
           for (int k = 0; k < U; ++k) any |= code[k] >= first && code[k] <= last;
@@ -1044,9 +1045,14 @@ __global__ __launch_bounds__(512) void k_overlap(const int32_t* va, const int32_
           int at[U];  // entries below the key (one less if all are); the searches advance together
 #pragma unroll
           for (int k = 0; k < U; ++k) at[k] = 0;
-          for (int step = len / 2; step > 0; step >>= 1) {
+          auto advance = [&](int step) {
 #pragma unroll
             for (int k = 0; k < U; ++k) at[k] += sb[at[k] + step - 1] < code[k] ? step : 0;
+          };
+          if (len == kOvChunk) {  // unrolled
+            for (int step = kOvChunk / 2; step > 0; step >>= 1) advance(step);
+          } else {
+            for (int step = len / 2; step > 0; step >>= 1) advance(step);
           }
 #pragma unroll
           for (int k = 0; k < U; ++k) cnt += sb[at[k]] == code[k] ? 1 : 0;
