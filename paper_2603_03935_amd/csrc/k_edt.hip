@@ -1223,11 +1223,14 @@ __device__ __forceinline__ void search_near(const uint2* base, us2 (&B)[4]) {
 // the tallest items, whose nearest edge is mostly at the side (2528 us without,
 // 2556 with, at 500 masks of 1920x1080).
 //
-// VALU-bound (62-74 % busy; the rest is the ends of packets, where few
-// wavefronts are left).  Kernel times, four rows and distances at a time without
-// the test / now: 16 frames of 1920x1080 with 500 masks, classes 0-4 1629 /
-// 1337 us, tall items 3159 / 2385 us; 64 frames of 640x480 with 60 masks 257 /
-// 229 us; 8 masks of 336x336 24.9 / 17.0 us.
+// VALU-bound (busy 79 % for items of at most 512 rows and 66 % for taller ones in
+// 16 frames of 1920x1080, 68 % in 64 frames of 640x480, 26 % in one frame, which
+// is one packet's latency; the rest is the ends of packets, where few wavefronts
+// are left).  Kernel times, four rows and distances at a time without the test /
+// now: 16 frames of 1920x1080 with 500 masks, classes 0-4 1621 / 1334 us, tall
+// items 3158 / 2325 us; 64 frames of 640x480 with 60 masks 257 / 231 us; 8 masks
+// of 336x336 24.1 / 16.9 us; noise of half the pixels, 300 masks of 640x480,
+// where eight rows search for the worst of them, 181 / 210.
 template <int PK, int MC>
 __device__ __forceinline__ void direct_group(const uint2* base, const uint16_t* mins, int blk, int last, int u0, int n,
                                              us2 (&E)[4]) {

@@ -320,11 +320,12 @@ __global__ __launch_bounds__(256) void k_sim(const float* emb, int m, const void
   }
 }
 
-// Tile by size (us of the whole query call at width 768 or 1024, 16 x 64 / 32
-// x 32 / 64 x 64, all with separate norms; the 64 x 64 kernel before, K step 16
-// and two barriers a step, took 182 us for 1024 x 8000 alone, now 145):
+// Tile by size (us of the whole query call at width 768 or 1024, 16 x 64 and 32 x
+// 32 with the norms on the way, 64 x 64 with their launch; the 64 x 64 kernel
+// before, K step 16 and two barriers a step, took 182 us for 1024 x 8000 alone,
+// now 145):
 //   q x m          5 x 20011   16 x 5000   64 x 3000   512 x 3000   1024 x 3000   1024 x 8000
-//                  31/34/49    20/19/32    17/17/25    49/45/49     94/87/76      210/189/165
+//                  24/26/48    17/17/26    17/16/26    54/47/50     95/82/71      226/200/163
 // Few queries are bound by reading the instances: the fewer of a tile's query
 // rows are padding, the better.  The larger tile reads less through LDS per
 // product but has a quarter of the workgroups and four times the chain of

@@ -10,8 +10,6 @@
 
 namespace disc {
 
-
-
 // Partial channel sums of one (frame, chunk): colsum_chunk (the device
 // helpers header); a standalone launch, or workgroups of the mask scan's
 // launch for small batches.
