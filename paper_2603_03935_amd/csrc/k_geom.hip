@@ -868,7 +868,7 @@ __device__ __forceinline__ uint64_t vox_code3(int x, int y, int z) {
 }
 
 // One workgroup per (segment, instance) pair.  The longer list is staged in
-// LDS, kOvChunk codes at a time, and every key of the shorter list is binary-
+// LDS, kOvPer codes per thread at a time, and every key of the shorter list is binary-
 // searched there, a thread's keys together.  With boxes, every list has been
 // cut into kOvParts runs of consecutive entries, and only the runs whose box
 // meets the box of a run of the other list are staged or searched: the lists
@@ -883,6 +883,16 @@ __device__ __forceinline__ uint64_t vox_code3(int x, int y, int z) {
 // pairs of 200 voxels took 16.4 us a call and 10000 of 100 36, so 13.4 and 29.
 // (The boxes' launch is not worth its 3 us there: 10.5 and 17 without boxes, by
 // 256 threads; the host does not know the lists' lengths.)
+// From kOvMany pairs on a workgroup has 256 threads and half the LDS: five of
+// them fit a CU, not three (registers), and the chain of dependent loads that a
+// pair of short lists is (pair, offsets, boxes, entries) waits beside more others:
+// 10000 pairs of 100 voxels 28 -> 20 us, of 800 32 -> 25, of 3000 41 -> 37.  Half
+// the chunk means twice the chunks, and every key was loaded for each, so long
+// lists were slower (6400 pairs of 9000 93 -> 122): a wavefront now goes from
+// chunk to chunk with the keys, which are sorted as the chunks are (93; 10000 of
+// 20000 387 -> 302).  With fewer pairs the larger workgroups are ahead on long
+// lists (4096 of 9000 77 / 84 us, 1024 of 9000 40 / 46), and in them that walk
+// costs registers and short lists 5 us.
 constexpr int kOvParts = 32;
 struct VoxBox {
   int32_t lo[3], hi[3];
@@ -919,7 +929,7 @@ __global__ __launch_bounds__(1024) void k_vox_boxes(const int32_t* va, const int
 }
 
 constexpr int kOvPer = 8;  // entries per thread and round, loaded together (1, 2 or 4 where they cover the list)
-constexpr int kOvChunk = 512 * kOvPer;
+constexpr int kOvMany = 6144;
 
 // The runs of a list that take part, as one list of n entries: pre[r] entries
 // come before run r.
@@ -935,14 +945,15 @@ __device__ __forceinline__ int ov_entry(const OvRuns& o, int t) {
   return o.first[r] + t;
 }
 
-template <int BOXES>
-__global__ __launch_bounds__(512) void k_overlap(const int32_t* va, const int32_t* oa, const int32_t* vb,
+template <int BOXES, int NT>
+__global__ __launch_bounds__(NT) void k_overlap(const int32_t* va, const int32_t* oa, const int32_t* vb,
                                                  const int32_t* ob, const int32_t* pairs, int na, int nb,
                                                  const VoxBox* boxes, int32_t* out) {
-  __shared__ uint64_t sb[kOvChunk];
+  constexpr int kChunk = NT * kOvPer;
+  __shared__ uint64_t sb[kChunk];
   __shared__ OvRuns runs[2];
   __shared__ uint32_t part[2];
-  __shared__ int red[8];
+  __shared__ int red[NT / 64];
   const int pr = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int i = pairs[2 * pr], j = pairs[2 * pr + 1];
   if (i < 0 || i >= na || j < 0 || j >= nb) {  // uniform over the workgroup
@@ -954,15 +965,16 @@ __global__ __launch_bounds__(512) void k_overlap(const int32_t* va, const int32_
   if (BOXES) {
     VoxBox* box = reinterpret_cast<VoxBox*>(sb);  // [2][kOvParts], before sb holds codes
     constexpr int W = sizeof(VoxBox) / 4 * kOvParts;
-    static_assert(2 * W <= 512 && 2 * kOvParts * kOvParts / 64 / 2 == 16, "boxes by one load per thread, two rounds of tests");
-    if (tid < 2 * W)
-      reinterpret_cast<int32_t*>(box)[tid] =
-          reinterpret_cast<const int32_t*>(boxes + (int64_t)(tid < W ? i : na + j) * kOvParts)[tid < W ? tid : tid - W];
+    static_assert(W <= NT && kOvParts * kOvParts % NT == 0, "a load per thread and list, full rounds of tests");
+    if (tid < W) {
+      reinterpret_cast<int32_t*>(box)[tid] = reinterpret_cast<const int32_t*>(boxes + (int64_t)i * kOvParts)[tid];
+      reinterpret_cast<int32_t*>(box)[W + tid] = reinterpret_cast<const int32_t*>(boxes + (int64_t)(na + j) * kOvParts)[tid];
+    }
     if (tid < 2) part[tid] = 0;
     __syncthreads();
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int t = tid + 512 * u;
+    for (int u = 0; u < kOvParts * kOvParts / NT; ++u) {
+      const int t = tid + NT * u;
       const VoxBox &x = box[t / kOvParts], &y = box[kOvParts + t % kOvParts];
       bool meet = true;
 #pragma unroll
@@ -1002,9 +1014,9 @@ __global__ __launch_bounds__(512) void k_overlap(const int32_t* va, const int32_
   const int kb = swap ? b0 : a0, tb = swap ? a0 : b0, nk = swap ? n1 : n0, nt = swap ? n0 : n1;
   // f with the number of entries per thread (1, 2, 4 or 8) that covers n entries, or a whole chunk
   auto per_thread = [&](int n, auto f) {
-    if (n <= 512) f(std::integral_constant<int, 1>{});
-    else if (n <= 1024) f(std::integral_constant<int, 2>{});
-    else if (n <= 2048) f(std::integral_constant<int, 4>{});
+    if (n <= NT) f(std::integral_constant<int, 1>{});
+    else if (n <= 2 * NT) f(std::integral_constant<int, 2>{});
+    else if (n <= 4 * NT) f(std::integral_constant<int, 4>{});
     else f(std::integral_constant<int, kOvPer>{});
   };
   // codes of entries t0 + 64 u of a list that takes part, `past` for those beyond its n entries
@@ -1019,7 +1031,8 @@ __global__ __launch_bounds__(512) void k_overlap(const int32_t* va, const int32_
   };
   int cnt = 0;
   if (nk > 0) {
-    for (int c0 = 0; c0 < nt; c0 += kOvChunk) {
+    int k0 = 0;  // where the wavefront begins: its keys of the rounds before lie below the chunk
+    for (int c0 = 0; c0 < nt; c0 += kChunk) {
       int len = 0;  // staged codes, a power of two
       per_thread(nt - c0, [&](auto u) {
         constexpr int U = decltype(u)::value;
@@ -1029,18 +1042,23 @@ __global__ __launch_bounds__(512) void k_overlap(const int32_t* va, const int32_
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < U; ++k) sb[64 * k + e0] = code[k];
-        len = 512 * U;
+        len = NT * U;
       });
       __syncthreads();
-      const uint64_t first = sb[0], last = sb[min(kOvChunk, nt - c0) - 1];
-      for (int k0 = 0; k0 < nk; k0 += kOvChunk)
-        per_thread(nk - k0, [&](auto u) {
+      const uint64_t first = sb[0], last = sb[min(kChunk, nt - c0) - 1];
+      for (int k1 = k0; k1 < nk; k1 += kChunk) {
+        bool past = false;  // its keys of the later rounds lie above the chunk
+        per_thread(nk - k1, [&](auto u) {
           constexpr int U = decltype(u)::value;
           uint64_t code[U];
-          load(u, kl, kb, runs[swap ? 1 : 0], nk, k0 + 64 * U * wv + lane, ~0ull, code);
+          load(u, kl, kb, runs[swap ? 1 : 0], nk, k1 + 64 * U * wv + lane, ~0ull, code);
           bool any = false;
 #pragma unroll
           for (int k = 0; k < U; ++k) any |= code[k] >= first && code[k] <= last;
+          if (NT == 256) {  // the keys ascend over the lanes, then over k
+            past = __shfl(code[0], 0) > last;
+            if (__shfl(code[U - 1], 63) <= last) k0 = k1 + kChunk;
+          }
           if (__ballot(any) == 0) return;
           int at[U];  // entries below the key (one less if all are); the searches advance together
 #pragma unroll
@@ -1049,14 +1067,16 @@ __global__ __launch_bounds__(512) void k_overlap(const int32_t* va, const int32_
 #pragma unroll
             for (int k = 0; k < U; ++k) at[k] += sb[at[k] + step - 1] < code[k] ? step : 0;
           };
-          if (len == kOvChunk) {  // unrolled
-            for (int step = kOvChunk / 2; step > 0; step >>= 1) advance(step);
+          if (len == kChunk) {  // unrolled
+            for (int step = kChunk / 2; step > 0; step >>= 1) advance(step);
           } else {
             for (int step = len / 2; step > 0; step >>= 1) advance(step);
           }
 #pragma unroll
           for (int k = 0; k < U; ++k) cnt += sb[at[k]] == code[k] ? 1 : 0;
         });
+        if (past) break;
+      }
     }
   }
   for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o);
@@ -1064,7 +1084,7 @@ __global__ __launch_bounds__(512) void k_overlap(const int32_t* va, const int32_
   __syncthreads();
   if (tid == 0) {
     int t = 0;
-    for (int w = 0; w < 8; ++w) t += red[w];
+    for (int w = 0; w < NT / 64; ++w) t += red[w];
     out[pr] = t;
   }
 }
@@ -1239,8 +1259,12 @@ void launch_overlap(const int32_t* va, const int32_t* oa, int na, const int32_t*
   for (int64_t p0 = 0; p0 < np; p0 += kPairs) {
     const dim3 grid((unsigned)std::min<int64_t>(kPairs, np - p0));
     const int32_t* pp = pairs + 2 * p0;
-    if (boxes) hipLaunchKernelGGL(k_overlap<1>, grid, dim3(512), 0, st, va, oa, vb, ob, pp, na, nb, boxes, out + p0);
-    else hipLaunchKernelGGL(k_overlap<0>, grid, dim3(512), 0, st, va, oa, vb, ob, pp, na, nb, nullptr, out + p0);
+    if (boxes && np >= kOvMany)
+      hipLaunchKernelGGL((k_overlap<1, 256>), grid, dim3(256), 0, st, va, oa, vb, ob, pp, na, nb, boxes, out + p0);
+    else if (boxes)
+      hipLaunchKernelGGL((k_overlap<1, 512>), grid, dim3(512), 0, st, va, oa, vb, ob, pp, na, nb, boxes, out + p0);
+    else
+      hipLaunchKernelGGL((k_overlap<0, 512>), grid, dim3(512), 0, st, va, oa, vb, ob, pp, na, nb, nullptr, out + p0);
   }
 }
 

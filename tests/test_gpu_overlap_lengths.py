@@ -11,13 +11,20 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("repeat", [1, 7])
 def test_lengths(repeat):
+    check([0, 1, 63, 65, 511, 512, 513, 1024, 1025, 2048, 2049, 4096, 4097, 4608, 8193], repeat)
+
+
+def test_lengths_of_many_pairs():
+    check([0, 1, 65, 255, 256, 257, 512, 513, 1024, 1025, 2047, 2048, 2049, 4096, 4097, 6145, 10000], 22)
+
+
+def check(sizes, repeat):
     t = torch()
     if not t.cuda.is_available():
         pytest.skip("no GPU")
     import paper_2603_03935_amd as disc
 
     rng = np.random.default_rng(8)
-    sizes = [0, 1, 63, 65, 511, 512, 513, 1024, 1025, 2048, 2049, 4096, 4097, 4608, 8193]
     lists = []
     for c in sizes:
         code = rng.choice(22 ** 3, size=c, replace=False)
