@@ -990,7 +990,7 @@ __device__ __forceinline__ void direct_table(int cls, const uint32_t* recs, cons
       for (int k4 = 0; k4 < kBlkRows; k4 += 4) {
         if (r0 + k4 >= it.n - 1) {  // padding rows only
           int pad = C * 0x10001u;
-          own(pad);
+          if (PK != 2) own(pad);
           gt[(k4 >> 2) * 64] = make_uint2((uint32_t)pad, (uint32_t)pad);
           high = splat2(C);
           block_done(k4);
@@ -1174,7 +1174,7 @@ __device__ __forceinline__ void search_step(const uint2* pu, const uint2* pd, in
 // u0 - 4 .. u0 + 11 of the table at base): all that a group of thin structures
 // needs, in half the loads and a third of the instructions of a step (300 masks
 // of 480 x 640, kernel: stripes 3 wide 160 / 133 us with this, lines 8 wide 74 /
-// 66, columns 9 wide 24.6 / 22.6).
+// 66, columns 9 wide 24.6 / 23.4).
 template <int PK>
 __device__ __forceinline__ void search_near(const uint2* base, us2 (&B)[4]) {
   uint32_t W[8];  // rows u0 - 4 + 2 j, u0 - 3 + 2 j
@@ -1259,7 +1259,11 @@ __device__ __forceinline__ void direct_group(const uint2* base, const uint16_t* 
   us2 worst = smallest();
   // no row further than five from the outside: distances of five and more improve none
   const bool near5 = __ballot((int)worst.x < C - 25) == 0;
-  if (near5 && __ballot((int)worst.x < C - 1) != 0) search_near<PK>(base, B);
+  if (near5 && __ballot((int)worst.x < C - 1) != 0) {
+    int none = 0;  // the near words' addresses are formed here (see own)
+    own(none);
+    search_near<PK>(base + none, B);
+  }
   if (!near5) {
     uint32_t near = (uint32_t)mins[blk * (64 / MC)] * 0x10001u, far = ends(0);
     // no candidate at d with d^2 >= C can improve a row
@@ -1310,7 +1314,6 @@ __device__ __forceinline__ void direct_packet(int cls, int s, int S, const uint3
     if (b >= live) break;
     if (ipp == 1) b = (live - 1) / 2 + ((b & 1) ? (b + 1) / 2 : -(b / 2));
     const int slot = b / nbs, lb = b - slot * nbs, b0 = lb * kBlkRows;
-    own(lane);
     const DirItem it = direct_item(recs, words, slot);
     const int n = it.n, P = it.P, y0 = it.y0;
     const int ua = max(b0, 1), ub = min(b0 + kBlkRows, n - 1);
@@ -1324,7 +1327,6 @@ __device__ __forceinline__ void direct_packet(int cls, int s, int S, const uint3
 #pragma unroll 1
     for (int gi = 0; gi < kBlkRows; gi += kDirRows) {
       if (b0 + gi >= ub) break;
-      own(lane);
       const uint2* base = gt_all + ((slot * rows_c + b0 + gi) >> 2) * 64 + lane;  // row u0 = b0 + gi
       us2 E[kDirRows / 2];
       direct_group<PK, MC>(base, m8 + lane / MC, (slot * rows_c + b0 + gi) >> 3,
