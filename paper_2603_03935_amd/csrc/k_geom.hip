@@ -560,21 +560,23 @@ __device__ __forceinline__ void db_point(const DbWork& d, int t, float e2, int m
 // other and as long as the slowest of its wavefront, took 213 + 62 us for 180k
 // points (eps 3 cm, 8 points), this 36 + 12 us.
 //
-// Where most cells hold a few points, there are too many items, each a chain of
-// loads for a handful of tests: then a thread per point (db_point), whose own
-// chain of 27 look-ups is the longer one but runs 64 to a wavefront.  The line
-// is where the items' chains outlast one round of the points' (us, 4 points,
-// items / points: 100k points in 63k cells 129 / 142, in 88k 190 / 170; 300k in
-// 130k 195 / 154, in 74k 115 / 110; 1M in 246k 286 / 223, in 317k 371 / 271; a
-// thread per point always 152, 212; 204, 153; 306, 356 before there were
-// items); min_pts = 1 is settled by the point itself.
+// Where most cells of a large cloud hold a point or two, there are too many
+// items, each a chain of loads for a handful of tests: then a thread per point
+// (db_point), whose own chain of 27 look-ups is the longer one (some 100 us) but
+// runs 64 to a wavefront.  The line is where the items' chains outlast one round
+// of the points' (us, items / points; points of depth images, 4 points: 67k in
+// 65k cells 110 / 142, 152k in 111k 205 / 227 and in 141k 236 / 224, 203k in 170k
+// 325 / 274, 456k in 190k 344 / 287, 608k in 146k 270 / 678, 1M in 230k 402 / 514
+// and in 490k 898 / 644, 4.1M in 792k 1411 / 1898; uniform clouds: 100k in 88k
+// 190 / 170, 300k in 130k 195 / 154, 1M in 317k 371 / 271); min_pts = 1 is
+// settled by the point itself.
 template <int PASS>
 __global__ __launch_bounds__(256) void k_db_cells(DbWork d, int n, float eps, int min_pts, int32_t* keep) {
 #pragma clang fp contract(off)
   const int lane = threadIdx.x & 63;
   const int nitems = d.total[1];
   const float e2 = eps * eps;
-  if (nitems > (min_pts == 1 ? 10000 : 30000 + n / 4)) {
+  if (nitems > (min_pts == 1 ? 10000 : 90000 + n / 5)) {
     for (int t = blockIdx.x * 256 + threadIdx.x; t < n; t += gridDim.x * 256) db_point<PASS>(d, t, e2, min_pts, keep);
     return;
   }

@@ -13,6 +13,17 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("segs,clustered,min_pts", [(60, 0.1, 4), (60, 0.1, 2), (60, 0.9, 4), (14, 0.3, 1), (60, 0.0, 12)])
 def test_sparse_cells(segs, clustered, min_pts):
+    cells, n = check(segs, clustered, min_pts)
+    assert (cells > (10000 if min_pts == 1 else 30000 + n // 4)) == (clustered < 0.5)
+
+
+@pytest.mark.parametrize("clustered,min_pts", [(0.1, 4), (0.1, 2), (0.5, 4), (0.7, 4), (0.0, 12)])
+def test_sparse_cells_of_large_clouds(clustered, min_pts):
+    cells, n = check(170, clustered, min_pts)
+    assert (cells > 90000 + n // 5) == (clustered < 0.6)
+
+
+def check(segs, clustered, min_pts):
     t = torch()
     if not t.cuda.is_available():
         pytest.skip("no GPU")
@@ -35,9 +46,9 @@ def test_sparse_cells(segs, clustered, min_pts):
         pts.append(p[rng.permutation(per)])
     p = np.concatenate(pts).astype(np.float32)
     n = len(p)
-    assert (cells > (10000 if min_pts == 1 else 30000 + n // 4)) == (clustered < 0.5)
     off = np.arange(segs + 1, dtype=np.int32) * per
     dp, do = t.from_numpy(p).cuda(), t.from_numpy(off).cuda()
     assert np.array_equal(disc.dbscan_denoise(dp, do, eps, min_pts).cpu().numpy(), og.dbscan_keep(p, off, eps, min_pts))
     dp[5] = float("nan")  # no neighbour, not even itself
     assert disc.dbscan_denoise(dp, do, eps, min_pts)[5].item() == 0
+    return cells, n
