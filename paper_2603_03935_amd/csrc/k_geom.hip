@@ -890,16 +890,15 @@ __device__ __forceinline__ uint64_t vox_code3(int x, int y, int z) {
 // pairs of 200 voxels took 16.4 us a call and 10000 of 100 36, so 13.4 and 29.
 // (The boxes' launch is not worth its 3 us there: 10.5 and 17 without boxes, by
 // 256 threads; the host does not know the lists' lengths.)
-// From kOvMany pairs on a workgroup has 256 threads and half the LDS: five of
+// A wavefront goes from chunk to chunk with its keys, which are sorted as the
+// chunks are; with every key loaded for every chunk 2 pairs of 100000 voxels took
+// 430 us and 2 of 300000 3072, so 116 and 285, 1024 of 9000 41, so 36.
+// From kOvMany pairs on a workgroup has 256 threads and half the LDS: six of
 // them fit a CU, not three (registers), and the chain of dependent loads that a
 // pair of short lists is (pair, offsets, boxes, entries) waits beside more others:
-// 10000 pairs of 100 voxels 28 -> 20 us, of 800 32 -> 25, of 3000 41 -> 37.  Half
-// the chunk means twice the chunks, and every key was loaded for each, so long
-// lists were slower (6400 pairs of 9000 93 -> 122): a wavefront now goes from
-// chunk to chunk with the keys, which are sorted as the chunks are (93; 10000 of
-// 20000 387 -> 302).  With fewer pairs the larger workgroups are ahead on long
-// lists (4096 of 9000 77 / 84 us, 1024 of 9000 40 / 46), and in them that walk
-// costs registers and short lists 5 us.
+// 10000 pairs of 100 voxels 28 -> 18 us, of 800 32 -> 22, of 3000 41 -> 35, of
+// 20000 387 -> 289.  With fewer pairs the larger workgroups are ahead on long
+// lists (4096 of 9000 69 / 84 us).
 constexpr int kOvParts = 32;
 struct VoxBox {
   int32_t lo[3], hi[3];
@@ -1062,10 +1061,8 @@ __global__ __launch_bounds__(NT) void k_overlap(const int32_t* va, const int32_t
           bool any = false;
 #pragma unroll
           for (int k = 0; k < U; ++k) any |= code[k] >= first && code[k] <= last;
-          if (NT == 256) {  // the keys ascend over the lanes, then over k
-            past = __shfl(code[0], 0) > last;
-            if (__shfl(code[U - 1], 63) <= last) k0 = k1 + kChunk;
-          }
+          past = __ballot(code[0] <= last) == 0;  // the keys ascend over the lanes, then over k
+          if (__ballot(code[U - 1] > last) == 0) k0 = k1 + kChunk;
           if (__ballot(any) == 0) return;
           int at[U];  // entries below the key (one less if all are); the searches advance together
 #pragma unroll
