@@ -564,19 +564,22 @@ __device__ __forceinline__ void db_point(const DbWork& d, int t, float e2, int m
 // items, each a chain of loads for a handful of tests: then a thread per point
 // (db_point), whose own chain of 27 look-ups is the longer one (some 100 us) but
 // runs 64 to a wavefront.  The line is where the items' chains outlast one round
-// of the points' (us, items / points; points of depth images, 4 points: 67k in
-// 65k cells 110 / 142, 152k in 111k 205 / 227 and in 141k 236 / 224, 203k in 170k
-// 325 / 274, 456k in 190k 344 / 287, 608k in 146k 270 / 678, 1M in 230k 402 / 514
-// and in 490k 898 / 644, 4.1M in 792k 1411 / 1898; uniform clouds: 100k in 88k
-// 190 / 170, 300k in 130k 195 / 154, 1M in 317k 371 / 271); min_pts = 1 is
-// settled by the point itself.
+// of the points' (whole call, us, items / points; points of depth images, 4
+// points: 73k in 61k cells 111 / 186, 152k in 141k 199 / 223, 203k in 171k 270 /
+// 276, 456k in 190k 293 / 282 and in 320k 498 / 416, 526k in 126k 250 / 378;
+// uniform clouds: 100k in 88k 147 / 168, 300k in 130k 163 / 155 and in 265k 358 /
+// 268); min_pts = 1 is settled by the point itself.
+//
+// The grid is what fits the chip at eight workgroups per CU, so the scalar
+// registers must not be what keeps the eighth out: with 85 of them 73k points in
+// 61k cells took 58 + 55 us, in two rounds, so 42 + 39.
 template <int PASS>
-__global__ __launch_bounds__(256) void k_db_cells(DbWork d, int n, float eps, int min_pts, int32_t* keep) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_num_sgpr(80))) void k_db_cells(DbWork d, int n, float eps, int min_pts, int32_t* keep) {
 #pragma clang fp contract(off)
   const int lane = threadIdx.x & 63;
   const int nitems = d.total[1];
   const float e2 = eps * eps;
-  if (nitems > (min_pts == 1 ? 10000 : 90000 + n / 5)) {
+  if (nitems > (min_pts == 1 ? 10000 : 130000 + n / 6)) {
     for (int t = blockIdx.x * 256 + threadIdx.x; t < n; t += gridDim.x * 256) db_point<PASS>(d, t, e2, min_pts, keep);
     return;
   }

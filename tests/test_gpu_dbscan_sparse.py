@@ -19,8 +19,8 @@ def test_sparse_cells(segs, clustered, min_pts):
 
 @pytest.mark.parametrize("clustered,min_pts", [(0.1, 4), (0.1, 2), (0.5, 4), (0.7, 4), (0.0, 12)])
 def test_sparse_cells_of_large_clouds(clustered, min_pts):
-    cells, n = check(170, clustered, min_pts)
-    assert (cells > 90000 + n // 5) == (clustered < 0.6)
+    cells, n = check(230, clustered, min_pts)
+    assert (cells > 130000 + n // 6) == (clustered < 0.6)
 
 
 def check(segs, clustered, min_pts):
