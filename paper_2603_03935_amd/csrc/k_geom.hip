@@ -558,7 +558,7 @@ __device__ __forceinline__ void db_point(const DbWork& d, int t, float e2, int m
 // point and 64 candidates) and the chain of loads per item.  A thread per
 // point that walked its 27 cells by itself, one dependent load after the
 // other and as long as the slowest of its wavefront, took 213 + 62 us for 180k
-// points (eps 3 cm, 8 points), this 36 + 12 us.
+// points (eps 3 cm, 8 points), this 32 + 12 us.
 //
 // Where most cells of a large cloud hold a point or two, there are too many
 // items, each a chain of loads for a handful of tests: then a thread per point
@@ -888,7 +888,7 @@ __device__ __forceinline__ uint64_t vox_code3(int x, int y, int z) {
 // coordinates within +-2^20 (the voxel sets above are within +-32767).
 //
 // 1296 pairs of 36 x 36 lists of up to 9000 voxels: 75 us with every pair's
-// longer list read by 256 threads, 29 us by boxes and 6 us to make them.  Of
+// longer list read by 256 threads, 25 us by boxes and 6 us to make them.  Of
 // short lists a thread takes one, two or four entries: with eight always, 1600
 // pairs of 200 voxels took 16.4 us a call and 10000 of 100 36, so 13.4 and 29.
 // (The boxes' launch is not worth its 3 us there: 10.5 and 17 without boxes, by
@@ -1253,7 +1253,7 @@ void launch_voxelize(const float* pts, const int32_t* off, const int32_t* keep, 
 // Boxes cost a launch and a pass over every list: they are made where every
 // list is in more than one pair on average and the pairs are more than run at
 // once (121 pairs of lists of some hundred voxels: 6 us without, 8 + 4 with;
-// 1296 of up to 9000 voxels: 75 without, 29 + 6 with).
+// 1296 of up to 9000 voxels: 75 without, 25 + 6 with).
 size_t overlap_ws_bytes(int na, int nb, int np) {
   return np > 512 && np > (int64_t)na + nb ? sizeof(VoxBox) * kOvParts * ((size_t)na + nb) : 0;
 }
